@@ -44,9 +44,11 @@
 // threads' streams, kernels of different streams no longer overlapped on the
 // device: four-stream serving went from 8 to 26 ms.)  Should a workgroup not
 // show up within WAIT_TICKS all the same (kernels of other processes that
-// wait like this, CUs masked off), whoever waits raises the abort flag,
-// everybody leaves, and the host runs the solve with the launch-per-step
-// loop; x is written only after the last meeting.
+// wait like this, CUs masked off), whoever waits gives the launch up, everybody
+// leaves, and the host runs the solve with the launch-per-step loop.  Results
+// are stored after the last meeting, by all workgroups or by none
+// (outcome.hpp): a launch's time may also be up in that meeting, when others
+// are past it.
 #include <condition_variable>
 #include <cmath>
 #include <cstdlib>
@@ -54,6 +56,7 @@
 #include <type_traits>
 
 #include "cg_common.hpp"
+#include "outcome.hpp"
 #include "wg_kernels.hpp"
 
 namespace dsm {
@@ -84,7 +87,7 @@ struct CgpArgs {
     int par;
     const double *dinv;
     u64 *slots;
-    u32 *abort_flag;
+    u32 *outcome;
     CgState *st, *host;
     double tol, pcont;
     long long maxit;
@@ -103,16 +106,27 @@ __device__ __forceinline__ void st_agent(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_slots_clear(u64 *slots, u32 *abort_flag) {
+__global__ void k_slots_clear(u64 *slots, u32 *outcome) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < SETS * SUMS * PG) slots[i] = EMPTY;
-    if (i == 0) *abort_flag = 0;
+    if (i == 0) *outcome = OUTCOME_OPEN;
 }
+
+// The launch's outcome (outcome.hpp).
+struct OutcomeWord {
+    u32 *p;
+    __device__ __forceinline__ u32 load() const { return ld_agent(p); }
+    __device__ __forceinline__ u32 swap(u32 from, u32 to) const {
+        __hip_atomic_compare_exchange_strong(p, &from, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        return from;
+    }
+};
 
 struct Meeting {
     u64 *slots;
-    u32 *abort_flag;
-    int *ok;  // LDS, 1 until a wait has failed
+    u32 *outcome;
+    int *ok;  // LDS: [0] is 1 until the launch has been given up, [1] the end of kept()
     WgSum total;
     int set = 0;
 
@@ -145,8 +159,7 @@ struct Meeting {
                     all = all && w[k] != EMPTY;
                 }
                 if (all) break;
-                if (tries % 64 == 0 && (wall_clock64() - t0 > WAIT_TICKS || ld_agent(abort_flag))) {
-                    st_agent(abort_flag, 1u);
+                if (tries % 64 == 0 && outcome_gives_up(OutcomeWord{outcome}, wall_clock64() - t0 > WAIT_TICKS)) {
                     *ok = 0;
                     break;
                 }
@@ -158,6 +171,13 @@ struct Meeting {
         asm volatile("" ::: "memory");
         return *ok != 0;
     }
+
+    // After the launch's last meeting: whether the results may be stored.
+    __device__ __forceinline__ bool kept() {
+        if (threadIdx.x == 0) ok[1] = outcome_keeps(OutcomeWord{outcome});
+        __syncthreads();
+        return ok[1] != 0;
+    }
 };
 
 // FMT: DSM_CSR, DSM_ELL or DSM_DIA.
@@ -165,7 +185,7 @@ template <class V, class X, int FMT, bool JAC>
 __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
     extern __shared__ __align__(16) char dyn[];
     __shared__ double sums[2 * NW];
-    __shared__ int ok;
+    __shared__ int ok[2];
     __shared__ i32 offs[FMT == DSM_DIA ? MAX_DIAGS : 1];
     __shared__ WaveRows wrows[NW];  // CSR: held in registers they cost spills
     const int tid = threadIdx.x;
@@ -183,7 +203,7 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
     X *r = (X *)A.r, *const pb[2] = {(X *)A.p[0], (X *)A.p[1]};
 
     if (tid == 0) {
-        ok = 1;
+        ok[0] = 1;
         pw[W] = 0;
     }
     if (FMT == DSM_CSR)
@@ -195,7 +215,7 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
         const WaveRows w = wave_rows(rows, rps);
         if (tid % WAVE == 0) wrows[tid / WAVE] = w;
     }
-    Meeting meet{A.slots, A.abort_flag, &ok, WgSum{sums}};
+    Meeting meet{A.slots, A.outcome, ok, WgSum{sums}};
 
     // The vector of a product, by column: src as it is, or the direction p =
     // z + beta src (z + nothing where there is no src), z = r or D^-1 r.
@@ -368,6 +388,7 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
         if (!meet(s)) return;
         rel_true = s[1] > 0 ? sqrt(s[0]) / sqrt(s[1]) : sqrt(s[0]);
     }
+    if (!meet.kept()) return;
     X *xo = (X *)(done ? A.x_out : A.x_work);
     for (int i = tid; i < rows; i += BB) {
         xo[r0 + i] = xs[i];
@@ -547,7 +568,7 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
     A.r = S.r;
     A.dinv = S.dinv;
     A.slots = (u64 *)S.meet;
-    A.abort_flag = (u32 *)(A.slots + SETS * SUMS * PG);
+    A.outcome = (u32 *)(A.slots + SETS * SUMS * PG);
     A.st = S.st;
     A.host = host_dev;
     A.tol = S.tol;
@@ -580,11 +601,11 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
             ~Cus() { share.give(n); }
         } cus(cu_share[m->ctx->device], G, ncu);
         host[0].done = -1;
-        hipLaunchKernelGGL(k_slots_clear, dim3(SETS * SUMS * PG / 256), dim3(256), 0, s, A.slots, A.abort_flag);
+        hipLaunchKernelGGL(k_slots_clear, dim3(SETS * SUMS * PG / 256), dim3(256), 0, s, A.slots, A.outcome);
         void *args[] = {&A};
         DSM_HIP(hipLaunchKernel(k, dim3(G), dim3(BB), args, lds, s));
         DSM_HIP(hipStreamSynchronize(s));
-        if (host[0].done < 0) {  // gave up; x_in and x_out are as they were
+        if (host[0].done < 0) {  // given up; x_in and x_out are as they were
             cgws.alone_wait = 64;
             return false;
         }
