@@ -1,6 +1,7 @@
 // C ABI: context, matrix lifecycle, conversion, inspection, export, SpMV.
 #include <algorithm>
 #include <cstdio>
+#include <exception>
 
 #include "core.hpp"
 
@@ -32,12 +33,8 @@ static size_t pool_class(dsm_ctx ctx, size_t bytes) {
 
 // Gives the oldest blocks back until at most `keep` bytes are held.
 static void pool_trim(dsm_ctx ctx, size_t keep) {
-    while (ctx->pool_bytes > keep) {
-        auto b = ctx->pool.front();
-        ctx->pool.pop_front();
-        ctx->pool_bytes -= b.bytes;
-        (void)hipFree(b.p);
-    }
+    BlockPool::Block b;
+    while (ctx->pool.bytes() > keep && ctx->pool.take_oldest(&b)) (void)hipFree(b.p);
 }
 
 void pool_release(dsm_ctx ctx) {
@@ -48,24 +45,21 @@ void pool_release(dsm_ctx ctx) {
 // A kept block of this class that is free of earlier work, or null.
 static void *pool_take(dsm_ctx ctx, size_t cls, hipStream_t s) {
     std::lock_guard<std::mutex> lk(ctx->pool_mu);
-    auto idle = [&](const dsm_ctx_s::PoolBlock &b) {
-        return b.seq <= ctx->pool_synced || (b.streamed && s != any_stream() && b.stream == s);
-    };
-    auto best = ctx->pool.end();
-    for (auto it = ctx->pool.begin(); it != ctx->pool.end(); ++it)
-        if (it->bytes == cls && (best == ctx->pool.end() || (idle(*it) && !idle(*best)))) best = it;
-    if (best == ctx->pool.end()) return nullptr;
-    if (!idle(*best)) {
-        if (hipSetDevice(ctx->device) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
+    BlockPool::Block b;
+    bool wait = false;
+    if (!ctx->pool.take(cls, s, &b, &wait)) return nullptr;
+    if (!wait) return b.p;
+    if (hipSetDevice(ctx->device) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        try {
+            ctx->pool.put(b.p, b.bytes, any_stream());
+        } catch (const std::bad_alloc &) {
+            (void)hipFree(b.p);
         }
-        ctx->pool_synced = ctx->pool_seq;
+        return nullptr;
     }
-    void *p = best->p;
-    ctx->pool_bytes -= cls;
-    ctx->pool.erase(best);
-    return p;
+    ctx->pool.waited(ctx->pool.frees());
+    return b.p;
 }
 
 void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s) {
@@ -112,9 +106,9 @@ void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s) {
         if (ctx->budget) keep = std::min(keep, ctx->budget - std::min(ctx->budget, ctx->in_use.load() - bytes));
         if (cls <= keep) {
             pool_trim(ctx, keep - cls);
-            ctx->pool.push_back({p, cls, s, s != any_stream(), ctx->pool_seq + 1});
-            ctx->pool_seq++;
-            ctx->pool_bytes += cls;
+            // while an error is on its way up the call's work may still be
+            // queued when it returns, and its stream may be destroyed
+            ctx->pool.put(p, cls, std::uncaught_exceptions() ? any_stream() : s);
             p = nullptr;
         }
     } catch (const std::bad_alloc &) {

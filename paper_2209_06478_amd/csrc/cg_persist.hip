@@ -459,7 +459,7 @@ static i64 reach_of(dsm_matrix m, hipStream_t s) {
         DSM_HIP(hipMemcpyAsync(&h, d, sizeof(int), hipMemcpyDeviceToHost, s));
         DSM_HIP(hipStreamSynchronize(s));
     } catch (...) {
-        dev_free(m->ctx, d, sizeof(int), s);
+        dev_free(m->ctx, d, sizeof(int));
         throw;
     }
     dev_free(m->ctx, d, sizeof(int), s);

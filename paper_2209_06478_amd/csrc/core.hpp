@@ -4,13 +4,13 @@
 #pragma once
 
 #include <atomic>
-#include <deque>
 #include <map>
 #include <mutex>
 #include <string>
 #include <vector>
 
 #include "common.hpp"
+#include "pool.hpp"
 
 struct dsm_ctx_s {
     // Effective bandwidth (GB/s) of the selection model's kernel classes
@@ -26,19 +26,9 @@ struct dsm_ctx_s {
     std::mutex cache_mu;                // selection cache
     std::map<std::string, std::pair<int, int>> select_cache;  // fingerprint -> (format, variant)
     // Freed device blocks kept for the next allocation of their size class
-    // (dev_alloc), oldest first.
-    struct PoolBlock {
-        void *p;
-        size_t bytes;        // size class
-        hipStream_t stream;  // every use was ordered on this stream, if `streamed`
-        bool streamed;
-        uint64_t seq;        // position in the order of frees
-    };
+    // (dev_alloc).
     std::mutex pool_mu;
-    std::deque<PoolBlock> pool;
-    size_t pool_bytes = 0;
-    uint64_t pool_seq = 0;     // frees so far
-    uint64_t pool_synced = 0;  // frees up to this one preceded a device synchronisation
+    dsm::BlockPool pool;
 };
 
 #include "admission.hpp"
@@ -52,9 +42,11 @@ namespace dsm {
 // budget has no room for an allocation and when the context is destroyed.
 // hipFree waits for the device; a kept block is handed out again only after
 // the same wait (once for all blocks freed before it), or without one when
-// both sides name the same stream.  `s`: all uses of the block are ordered on
-// this stream (any_stream(): not known).
-inline hipStream_t any_stream() { return (hipStream_t)(uintptr_t)-1; }
+// both sides name the same stream (pool.hpp).  `s`: all uses of the block are
+// ordered on this stream (any_stream(): not known), and the call that frees it
+// waits for the stream before it returns, so that no work is left on it should
+// the caller destroy it and its handle come back.
+inline hipStream_t any_stream() { return (hipStream_t)BlockPool::unknown(); }
 void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s = any_stream());
 void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s = any_stream());
 void pool_release(dsm_ctx ctx);

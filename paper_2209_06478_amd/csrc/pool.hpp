@@ -1,0 +1,73 @@
+// Freed device blocks kept for later allocations: the bookkeeping alone (no
+// HIP, no lock), so that it can be checked on the CPU.
+//
+// A block may still be in use by work queued before it was freed.  It is idle,
+// and handed out as it is, when a device-wide wait followed its free or when
+// all its uses and the next ones are ordered on one stream.  A stream is known
+// by its handle, so a handle must stand for one stream only: the per-thread
+// default stream, one handle for a stream of each thread, is never that.
+#pragma once
+
+#include <cstddef>
+#include <cstdint>
+#include <deque>
+
+namespace dsm {
+
+class BlockPool {
+public:
+    using Stream = const void *;
+    static Stream unknown() { return (Stream)(uintptr_t)-1; }
+    static Stream per_thread() { return (Stream)(uintptr_t)2; }
+
+    struct Block {
+        void *p;
+        size_t bytes;    // size class
+        Stream stream;   // every use was ordered on it; unknown() otherwise
+        uint64_t seq;    // position in the order of frees
+    };
+
+    size_t bytes() const { return held; }
+    uint64_t frees() const { return last; }
+
+    void put(void *p, size_t bytes, Stream s) {
+        blocks.push_back({p, bytes, ordered(s) ? s : unknown(), last + 1});
+        last++;
+        held += bytes;
+    }
+
+    // A block of this class, an idle one if there is any; false without one.
+    // *wait: it is not idle.
+    bool take(size_t bytes, Stream s, Block *out, bool *wait) {
+        auto best = blocks.end();
+        for (auto it = blocks.begin(); it != blocks.end(); ++it)
+            if (it->bytes == bytes && (best == blocks.end() || (idle(*it, s) && !idle(*best, s)))) best = it;
+        if (best == blocks.end()) return false;
+        *out = *best;
+        *wait = !idle(*best, s);
+        held -= bytes;
+        blocks.erase(best);
+        return true;
+    }
+
+    bool take_oldest(Block *out) {
+        if (blocks.empty()) return false;
+        *out = blocks.front();
+        held -= out->bytes;
+        blocks.pop_front();
+        return true;
+    }
+
+    // The device has been waited for after the `upto`-th free.
+    void waited(uint64_t upto) { synced = upto > synced ? upto : synced; }
+
+private:
+    std::deque<Block> blocks;  // oldest first
+    size_t held = 0;
+    uint64_t last = 0, synced = 0;
+
+    static bool ordered(Stream s) { return s != unknown() && s != per_thread(); }
+    bool idle(const Block &b, Stream s) const { return b.seq <= synced || (ordered(s) && b.stream == s); }
+};
+
+}  // namespace dsm

@@ -109,7 +109,7 @@ static i64 scan_impl(dsm_ctx ctx, const InT *in, OutT *out, i64 n, hipStream_t s
         try {
             scan_impl<i64, i64>(ctx, sums, offs, ntiles, s, false);
         } catch (...) {
-            dev_free(ctx, offs, obytes, s);
+            dev_free(ctx, offs, obytes);
             throw;
         }
     }
@@ -162,7 +162,7 @@ i32 reduce_max_i32(dsm_ctx ctx, const i32 *in, i64 n, hipStream_t s) {
         DSM_HIP(hipMemcpyAsync(&h, part + g, sizeof(i32), hipMemcpyDeviceToHost, s));
         DSM_HIP(hipStreamSynchronize(s));
     } catch (...) {
-        dev_free(ctx, part, sizeof(i32) * (g + 1), s);
+        dev_free(ctx, part, sizeof(i32) * (g + 1));
         throw;
     }
     dev_free(ctx, part, sizeof(i32) * (g + 1), s);

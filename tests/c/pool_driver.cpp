@@ -1,0 +1,62 @@
+// When a kept device block may be handed out without a wait (pool.hpp).
+// Prints "pool driver ok" and exits 0 when every check holds.
+#include <cstdio>
+#include <cstring>
+
+#include "../../paper_2209_06478_amd/csrc/pool.hpp"
+
+using dsm::BlockPool;
+
+static int fails = 0;
+#define CHECK(c)                                                         \
+    do {                                                                 \
+        if (!(c)) {                                                      \
+            std::printf("FAILED %s:%d: %s\n", __FILE__, __LINE__, #c);   \
+            fails++;                                                     \
+        }                                                                \
+    } while (0)
+
+static char mem[16];
+static int handle[2];
+
+int main() {
+    BlockPool::Block b;
+    bool wait = false;
+    const BlockPool::Stream null = nullptr, s0 = &handle[0], s1 = &handle[1], per = BlockPool::per_thread(),
+                            any = BlockPool::unknown();
+    // freed on a row, wanted on a column: a wait unless both are one known stream
+    const BlockPool::Stream st[5] = {null, s0, s1, per, any};
+    for (int i = 0; i < 5; i++)
+        for (int j = 0; j < 5; j++) {
+            BlockPool p;
+            p.put(mem, 256, st[i]);
+            CHECK(p.bytes() == 256 && !p.take(512, st[j], &b, &wait));
+            CHECK(p.take(256, st[j], &b, &wait) && b.p == mem && p.bytes() == 0);
+            CHECK(wait == !(i == j && st[i] != per && st[i] != any));
+        }
+    // a device-wide wait serves the frees before it, not those after
+    for (BlockPool::Stream s : st) {
+        BlockPool p;
+        p.put(mem, 256, s);
+        p.waited(p.frees());
+        p.put(mem + 1, 256, any);
+        CHECK(p.take(256, any, &b, &wait) && b.p == mem && !wait);
+        CHECK(p.take(256, any, &b, &wait) && b.p == mem + 1 && wait);
+    }
+    // an idle block goes before an older one that is not; the oldest goes back first
+    {
+        BlockPool p;
+        p.put(mem, 256, s0);
+        p.put(mem + 1, 256, s1);
+        p.put(mem + 2, 512, s1);
+        CHECK(p.take(256, s1, &b, &wait) && b.p == mem + 1 && !wait);
+        CHECK(p.take_oldest(&b) && b.p == mem && p.take_oldest(&b) && b.p == mem + 2 && !p.take_oldest(&b));
+        CHECK(p.bytes() == 0 && p.frees() == 3);
+        p.waited(2);
+        p.waited(1);  // (waits end in any order)
+        p.put(mem, 256, any);
+        CHECK(p.take(256, any, &b, &wait) && wait);
+    }
+    if (!fails) std::printf("pool driver ok\n");
+    return fails != 0;
+}
