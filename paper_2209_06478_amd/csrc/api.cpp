@@ -42,24 +42,31 @@ void pool_release(dsm_ctx ctx) {
     pool_trim(ctx, 0);
 }
 
-// A kept block of this class that is free of earlier work, or null.
+// A kept block of this class that is free of earlier work, or null.  The
+// device is waited for without the lock: other threads go on meanwhile.
 static void *pool_take(dsm_ctx ctx, size_t cls, hipStream_t s) {
-    std::lock_guard<std::mutex> lk(ctx->pool_mu);
     BlockPool::Block b;
     bool wait = false;
-    if (!ctx->pool.take(cls, s, &b, &wait)) return nullptr;
-    if (!wait) return b.p;
-    if (hipSetDevice(ctx->device) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-        (void)hipGetLastError();
-        try {
-            ctx->pool.put(b.p, b.bytes, any_stream());
-        } catch (const std::bad_alloc &) {
-            (void)hipFree(b.p);
-        }
-        return nullptr;
+    uint64_t before;
+    {
+        std::lock_guard<std::mutex> lk(ctx->pool_mu);
+        if (!ctx->pool.take(cls, s, &b, &wait)) return nullptr;
+        before = ctx->pool.frees();
     }
-    ctx->pool.waited(ctx->pool.frees());
-    return b.p;
+    if (!wait) return b.p;
+    const bool ok = hipSetDevice(ctx->device) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+    std::lock_guard<std::mutex> lk(ctx->pool_mu);
+    if (ok) {
+        ctx->pool.waited(before);
+        return b.p;
+    }
+    (void)hipGetLastError();
+    try {
+        ctx->pool.put(b.p, b.bytes, any_stream());
+    } catch (const std::bad_alloc &) {
+        (void)hipFree(b.p);
+    }
+    return nullptr;
 }
 
 void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s) {
@@ -96,7 +103,7 @@ void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s) {
     return p;
 }
 
-void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s) {
+void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s, bool unused) {
     if (!p) return;
     if (bytes == 0) bytes = 16;
     const size_t cls = pool_class(ctx, bytes);
@@ -108,7 +115,7 @@ void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s) {
             pool_trim(ctx, keep - cls);
             // while an error is on its way up the call's work may still be
             // queued when it returns, and its stream may be destroyed
-            ctx->pool.put(p, cls, std::uncaught_exceptions() ? any_stream() : s);
+            ctx->pool.put(p, cls, std::uncaught_exceptions() ? any_stream() : s, unused);
             p = nullptr;
         }
     } catch (const std::bad_alloc &) {
@@ -159,10 +166,10 @@ void ws_release_host(Workspace &w) {
     w.host = nullptr;
 }
 
-void ws_release(dsm_ctx ctx, Workspace &w) {
+void ws_release(dsm_ctx ctx, Workspace &w, bool unused) {
     ws_release_host(w);
     if (w.p) {
-        dev_free(ctx, w.p, w.bytes);
+        dev_free(ctx, w.p, w.bytes, any_stream(), unused);
         if (w.live) *w.live -= w.bytes;
     }
     w.p = nullptr;
@@ -250,10 +257,11 @@ static dsm_matrix new_matrix(dsm_ctx ctx, int64_t nrows, int64_t ncols, int64_t 
 }
 
 static void free_matrix(dsm_matrix m) {
-    (void)hipDeviceSynchronize();
-    m->P.release(m->ctx);
-    ws_release(m->ctx, m->ws);
-    ws_release(m->ctx, m->cgws);
+    // nothing uses its memory after this wait: the next handle takes it as it is
+    const bool unused = hipDeviceSynchronize() == hipSuccess;
+    m->P.release(m->ctx, unused);
+    ws_release(m->ctx, m->ws, unused);
+    ws_release(m->ctx, m->cgws, unused);
     m->ctx->live_matrices--;
     delete m;
 }

@@ -45,10 +45,11 @@ namespace dsm {
 // both sides name the same stream (pool.hpp).  `s`: all uses of the block are
 // ordered on this stream (any_stream(): not known), and the call that frees it
 // waits for the stream before it returns, so that no work is left on it should
-// the caller destroy it and its handle come back.
+// the caller destroy it and its handle come back.  unused: the device has been
+// waited for since the block's last use.
 inline hipStream_t any_stream() { return (hipStream_t)BlockPool::unknown(); }
 void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s = any_stream());
-void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s = any_stream());
+void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s = any_stream(), bool unused = false);
 void pool_release(dsm_ctx ctx);
 // A number no other payload has had (0 is none).
 uint64_t next_payload_id();
@@ -103,8 +104,8 @@ struct Payload {
         bytes += b;
         return p;
     }
-    void release(dsm_ctx ctx) {
-        for (auto &pb : bufs) dev_free(ctx, pb.first, pb.second);
+    void release(dsm_ctx ctx, bool unused = false) {
+        for (auto &pb : bufs) dev_free(ctx, pb.first, pb.second, any_stream(), unused);
         bufs.clear();
         bytes = 0;
         *this = Payload();
@@ -154,7 +155,7 @@ namespace dsm {
 // the stream `s` of the call and the workspace's own replay stream are
 // synchronised (not the whole device).
 void *ws_get(dsm_ctx ctx, Workspace &w, size_t bytes, hipStream_t s);
-void ws_release(dsm_ctx ctx, Workspace &w);
+void ws_release(dsm_ctx ctx, Workspace &w, bool unused = false);
 // Releases a workspace's graph, stream, events and pinned host staging;
 // its device memory stays.
 void ws_release_host(Workspace &w);

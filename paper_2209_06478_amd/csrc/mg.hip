@@ -84,10 +84,10 @@ struct dsm_mg_s {
         bufs.push_back({p, b});
         return p;
     }
-    void release() {
-        for (auto &l : L) dsm::ws_release(ctx, l.spws);
+    void release(bool unused = false) {
+        for (auto &l : L) dsm::ws_release(ctx, l.spws, unused);
         dsm::ws_release_host(gws);
-        for (auto &b : bufs) dsm::dev_free(ctx, b.first, b.second);
+        for (auto &b : bufs) dsm::dev_free(ctx, b.first, b.second, dsm::any_stream(), unused);
         bufs.clear();
     }
 };
@@ -1293,8 +1293,7 @@ DSM_API dsm_status dsm_mg_destroy(dsm_mg mg) {
     return guard([&] {
         if (!mg) return;
         (void)hipSetDevice(mg->ctx->device);
-        (void)hipDeviceSynchronize();
-        mg->release();
+        mg->release(hipDeviceSynchronize() == hipSuccess);
         delete mg;
     });
 }

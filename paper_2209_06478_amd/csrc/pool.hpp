@@ -2,8 +2,8 @@
 // HIP, no lock), so that it can be checked on the CPU.
 //
 // A block may still be in use by work queued before it was freed.  It is idle,
-// and handed out as it is, when a device-wide wait followed its free or when
-// all its uses and the next ones are ordered on one stream.  A stream is known
+// and handed out as it is, when a device-wide wait followed its last use or
+// its free, or when all its uses and the next ones are ordered on one stream.  A stream is known
 // by its handle, so a handle must stand for one stream only: the per-thread
 // default stream, one handle for a stream of each thread, is never that.
 #pragma once
@@ -24,14 +24,15 @@ public:
         void *p;
         size_t bytes;    // size class
         Stream stream;   // every use was ordered on it; unknown() otherwise
-        uint64_t seq;    // position in the order of frees
+        uint64_t seq;    // position in the order of frees; 0: idle
     };
 
     size_t bytes() const { return held; }
     uint64_t frees() const { return last; }
 
-    void put(void *p, size_t bytes, Stream s) {
-        blocks.push_back({p, bytes, ordered(s) ? s : unknown(), last + 1});
+    // unused: the device has been waited for since the last use
+    void put(void *p, size_t bytes, Stream s, bool unused = false) {
+        blocks.push_back({p, bytes, ordered(s) ? s : unknown(), unused ? 0 : last + 1});
         last++;
         held += bytes;
     }

@@ -57,6 +57,14 @@ int main() {
         p.put(mem, 256, any);
         CHECK(p.take(256, any, &b, &wait) && wait);
     }
+    // put back after a device-wide wait: idle at once, whatever is freed later
+    {
+        BlockPool p;
+        p.put(mem, 256, any, true);
+        p.put(mem + 1, 256, any);
+        CHECK(p.take(256, any, &b, &wait) && b.p == mem && !wait);
+        CHECK(p.take(256, any, &b, &wait) && wait);
+    }
     if (!fails) std::printf("pool driver ok\n");
     return fails != 0;
 }
