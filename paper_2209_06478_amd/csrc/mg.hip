@@ -208,7 +208,9 @@ __global__ void __launch_bounds__(MB) k_symgs_dia(i64 t0, i64 cnt, const i32 *__
 //    is still zero (the same bits: the level's values are finite);
 //  - the forward part keeps the sum over the lower colours, and the backward
 //    part resumes it with the higher ones only, since a row's lower
-//    neighbours have not changed in between.
+//    neighbours have not changed in between.  The sums lie in the hierarchy, so
+//    only a V-cycle's sweeps do so; a sweep by itself, which may run beside
+//    others, reads all of them and has the same bits.
 // A V-cycle's two sweeps then read 520 instead of 754 values per eight rows;
 // the sum runs over the lower part, then the higher, instead of ascending.
 // cap >= 0: keep[t] is the sum over the first cap diagonals; resume: the sum
@@ -909,8 +911,10 @@ static void list_launch(const dsm_mg_s::Level &lv, int c, int at, int no, const 
 // One symmetric Gauss-Seidel sweep on level l: x <- S(x) for A_l x = r.
 // from_zero: x is first set to zero (the pre-smoothing of a V-cycle), folded
 // into the sweep's first launch, or already into an earlier one (started).
-// Then x is added to `to`, if it is given, by the last launch.
-static void symgs(dsm_mg_s *mg, int l, const double *r, double *x, hipStream_t s, const int *stop,
+// Then x is added to `to`, if it is given, by the last launch.  shared: the
+// sweep may use the hierarchy's buffers (a V-cycle's; not a sweep by itself,
+// of which several may run at a time).
+static void symgs(dsm_mg_s *mg, int l, const double *r, double *x, hipStream_t s, const int *stop, bool shared,
                   bool from_zero = false, bool started = false, const Prolong &to = {}) {
     auto &lv = mg->L[l];
     const Payload &P = lv.A->P;
@@ -957,7 +961,7 @@ static void symgs(dsm_mg_s *mg, int l, const double *r, double *x, hipStream_t s
             const Prolong last = k + 1 == order.size() ? to : Prolong{};
             added = last.f2c != nullptr;
             const int nod = (int)P.ndiag - 1, low = lv.nlow.empty() ? 0 : lv.nlow[c];
-            if (lv.nlow.empty()) list_launch<2>(lv, c, 0, nod, r, x, -1, false, last, s, stop);
+            if (lv.nlow.empty() || !shared) list_launch<2>(lv, c, 0, nod, r, x, -1, false, last, s, stop);
             else if (k < forward)
                 list_launch<2>(lv, c, 0, from_zero ? low : nod, r, x, low ? low : -1, false, last, s, stop);
             else  // (without higher ones nothing is summed, but the kernel reads two copies)
@@ -996,7 +1000,7 @@ static void vcycle(dsm_mg_s *mg, int l, const double *r, double *x, hipStream_t 
                    bool started = false, const Prolong &to = {}) {
     auto &lv = mg->L[l];
     const bool coarsest = l + 1 == (int)mg->L.size();
-    if (lv.cstart.size() > 1) symgs(mg, l, r, x, s, stop, true, started, coarsest ? to : Prolong{});
+    if (lv.cstart.size() > 1) symgs(mg, l, r, x, s, stop, true, true, started, coarsest ? to : Prolong{});
     else hipLaunchKernelGGL(k_mg_zero, dim3(grid_for(lv.n, MB)), dim3(MB), 0, s, lv.n, x, stop);
     if (coarsest) return;
     auto &cv = mg->L[l + 1];
@@ -1013,7 +1017,7 @@ static void vcycle(dsm_mg_s *mg, int l, const double *r, double *x, hipStream_t 
         hipLaunchKernelGGL(k_restrict_csr<GSW>, dim3(grid_for(cv.n * GSW, MB)), dim3(MB), 0, s, cv.n, lv.f2c, P.rp,
                            P.col, (const double *)P.val, x, r, cv.r, first, cv.x, stop);
     vcycle(mg, l + 1, cv.r, cv.x, s, stop, first != nullptr, {lv.f2c, x});
-    symgs(mg, l, r, x, s, stop, false, false, to);
+    symgs(mg, l, r, x, s, stop, true, false, false, to);
     DSM_HIP(hipGetLastError());
 }
 
@@ -1307,7 +1311,7 @@ DSM_API dsm_status dsm_mg_symgs(dsm_mg mg, int32_t level, const double *r, doubl
         DSM_CHECK(r != x || lv.n == 0, DSM_E_INVALID, "r and x must not alias");
         check_level_format(lv);
         DSM_HIP(hipSetDevice(mg->ctx->device));
-        if (lv.n > 0) symgs(mg, level, r, x, (hipStream_t)stream, nullptr);
+        if (lv.n > 0) symgs(mg, level, r, x, (hipStream_t)stream, nullptr, false);
     });
 }
 
