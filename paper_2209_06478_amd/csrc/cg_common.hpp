@@ -110,15 +110,17 @@ struct FlagSum {
 bool cg_graphs_enabled();
 
 // A solve by the one-launch loop (cg_persist.hip): b, x and the work vectors
-// p, r, x_work of one type; `meet` holds cg_persist_bytes() of scratch.
+// p, r, q, x_work of one type; `meet` holds cg_persist_bytes() of scratch, part
+// 768 doubles.
 template <class X>
 struct CgpSolve {
     const X *b, *x_in;
-    X *x_out, *x_work, *p[2], *r;
+    X *x_out, *x_work, *p[2], *r, *q;
     int par;             // the direction of iteration k ends in p[(k + par) & 1]; pcont != 0:
                          // the direction to continue is in p[par & 1]
     const double *dinv;  // Jacobi's inverse diagonal, or null
     void *meet;
+    double *part;
     CgState *st;
     double tol, pcont;
     long long maxit;
@@ -126,10 +128,10 @@ struct CgpSolve {
     int every;     // iterations per launch; <= 0: chosen by size
 };
 size_t cg_persist_bytes();
-// Solves and waits; false, with x_out untouched, when the system does not fit
-// that loop or the device could not hold the launch at once (the solves in
-// flight on a device share its CUs; a solve waits for its turn).  rel_true (or
-// null) receives ||b - A x|| / ||b||.
+// Solves and waits; false, with nothing done, when the system does not fit that
+// loop.  The solves in flight on a device share its CUs (a solve waits for its
+// turn); one whose launch could not be held at once all the same goes on step by
+// step, with the same bits.  rel_true (or null) receives ||b - A x|| / ||b||.
 template <class X>
 bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cgws, CgState *out, double *rel_true);
 

@@ -44,11 +44,13 @@
 // threads' streams, kernels of different streams no longer overlapped on the
 // device: four-stream serving went from 8 to 26 ms.)  Should a workgroup not
 // show up within WAIT_TICKS all the same (kernels of other processes that
-// wait like this, CUs masked off), whoever waits gives the launch up, everybody
-// leaves, and the host runs the solve with the launch-per-step loop.  Results
-// are stored after the last meeting, by all workgroups or by none
-// (outcome.hpp): a launch's time may also be up in that meeting, when others
-// are past it.
+// wait like this, CUs masked off), whoever waits gives the launch up and
+// everybody leaves.  Results are stored after the last meeting, by all
+// workgroups or by none (outcome.hpp): a launch's time may also be up in that
+// meeting, when others are past it.  The solve then goes on from the last
+// launch that was kept, a step per launch instead of a meeting (PHASE_*): the
+// same workgroups with the same rows and sums in the same order, so its bits
+// do not depend on what else the device was doing.
 #include <condition_variable>
 #include <cmath>
 #include <cstdlib>
@@ -67,6 +69,10 @@ constexpr int MAX_DIAGS = 1024;           // DIA offsets kept in LDS
 constexpr u64 EMPTY = 0x7ff4dead7ff4deadull;
 constexpr u64 NAN_WORD = 0x7ff8000000000000ull;
 constexpr long long WAIT_TICKS = 10000000;  // of the 100 MHz clock: 0.1 s
+constexpr int ALONE = 64;                 // solves that go by steps after one that was given up
+
+// The steps of a solve between meetings, as launches of their own.
+enum { PHASE_INIT, PHASE_PQ, PHASE_RR, PHASE_TRUE };
 
 struct CgpArgs {
     int n, rpw;  // rows, rows per workgroup (a multiple of 64)
@@ -82,7 +88,7 @@ struct CgpArgs {
     // vectors
     const void *b, *x_in;
     void *x_out, *x_work;  // where x goes when the solve is done, and before
-    void *p[2];  // p of iteration k, after it in p[(k + par) & 1]
+    void *p[2];  // p of iteration k, after it in p[(k + par) & 1]; an unfinished launch leaves r in the other
     void *r;
     int par;
     const double *dinv;
@@ -95,6 +101,10 @@ struct CgpArgs {
     int resume;   // x_work, r, p and *st hold an unfinished solve
     int x0_zero;  // x_in is zero (and not read)
     int want_true;
+    // a solve by steps
+    void *q;
+    double *part;  // the workgroups' sums: PG of each of three
+    int phase;
 };
 
 template <class T>
@@ -106,10 +116,10 @@ __device__ __forceinline__ void st_agent(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_slots_clear(u64 *slots, u32 *outcome) {
+__global__ void k_slots_clear(u64 *slots, u32 *outcome, u32 open) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < SETS * SUMS * PG) slots[i] = EMPTY;
-    if (i == 0) *outcome = OUTCOME_OPEN;
+    if (i == 0) *outcome = open;
 }
 
 // The launch's outcome (outcome.hpp).
@@ -180,8 +190,9 @@ struct Meeting {
     }
 };
 
-// FMT: DSM_CSR, DSM_ELL or DSM_DIA.
-template <class V, class X, int FMT, bool JAC>
+// FMT: DSM_CSR, DSM_ELL or DSM_DIA.  STEP: one step of the solve (A.phase)
+// instead of its loop, its vectors in memory between steps.
+template <class V, class X, int FMT, bool JAC, bool STEP>
 __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
     extern __shared__ __align__(16) char dyn[];
     __shared__ double sums[2 * NW];
@@ -279,6 +290,78 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
     };
     auto publish = [&](X *to, int i, X v) { st_agent(to + r0 + i, v); };
 
+    if constexpr (STEP) {
+        WgSum total{sums};
+        auto put = [&](int k, double v) {
+            v = total(v);
+            if (tid == 0) A.part[k * PG + blockIdx.x] = v;
+        };
+        X *const xw = (X *)A.x_work, *const q = (X *)A.q;
+        double s[2] = {0, 0};
+        if (A.phase == PHASE_INIT) {
+            if (!A.x0_zero) {
+                for (int i = tid; i < rows; i += BB) ps[i] = xs[i] = ((const X *)A.x_in)[r0 + i];
+                product(Vec{(const X *)A.x_in, false, (X)0});
+            }
+            for (int i = tid; i < rows; i += BB) {
+                const X ri = A.x0_zero ? b[r0 + i] : b[r0 + i] - qs[i];
+                xw[r0 + i] = A.x0_zero ? (X)0 : xs[i];
+                r[r0 + i] = ri;
+                s[0] += JAC ? (double)ri * ((double)ri * dinv(r0 + i)) : (double)ri * (double)ri;
+                s[1] += (double)ri * (double)ri;
+            }
+            put(0, s[0]);
+            put(1, s[1]);
+            return;
+        }
+        if (A.phase == PHASE_TRUE) {
+            for (int i = tid; i < rows; i += BB) ps[i] = xw[r0 + i];
+            product(Vec{xw, false, (X)0});
+            for (int i = tid; i < rows; i += BB) {
+                const double bi = (double)b[r0 + i], d = bi - (double)qs[i];
+                s[0] += d * d;
+                s[1] += bi * bi;
+            }
+            put(0, s[0]);
+            put(1, s[1]);
+            return;
+        }
+        if (A.st->done) return;  // (the steps' kernels do not write it)
+        const long long k = A.st->iters;
+        if (A.phase == PHASE_PQ) {
+            Vec v{nullptr, true, (X)0};
+            if (k > 0) v = Vec{pb[(k + A.par) & 1], true, (X)(A.st->rho[k & 1] / A.st->rho[(k & 1) ^ 1])};
+            else if (A.pcont != 0) v = Vec{pb[A.par & 1], true, (X)A.pcont};
+            for (int t = tid; v.src && t < W; t += BB) {
+                const int j = r0 - win + t;
+                pw[t] = j >= 0 && j < A.n ? v.src[j] : (X)0;
+            }
+            __syncthreads();
+            for (int i = tid; i < rows; i += BB) ps[i] = direction(v, precond(r[r0 + i], r0 + i), ps[i]);
+            product(v);
+            X *const pn = pb[(k + 1 + A.par) & 1];
+            for (int i = tid; i < rows; i += BB) {
+                pn[r0 + i] = ps[i];
+                q[r0 + i] = qs[i];
+                s[0] += (double)ps[i] * (double)qs[i];
+            }
+            put(2, s[0]);
+        } else {  // PHASE_RR
+            const X alpha = (X)(A.st->rho[(k & 1) ^ 1] / A.st->pq);
+            const X *const p = pb[(k + A.par) & 1];
+            for (int i = tid; i < rows; i += BB) {
+                xw[r0 + i] = xw[r0 + i] + alpha * p[r0 + i];
+                const X ri = r[r0 + i] - alpha * q[r0 + i];
+                r[r0 + i] = ri;
+                s[0] += JAC ? (double)ri * ((double)ri * dinv(r0 + i)) : (double)ri * (double)ri;
+                s[1] += (double)ri * (double)ri;
+            }
+            put(0, s[0]);
+            if (JAC) put(1, s[1]);
+        }
+        return;
+    }
+
     double rho, nr0, relres;
     double rho_last = 0, pq_last = 0;  // rho before the last iteration
     long long k = 0;
@@ -371,14 +454,14 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
     }
     double rel_true = 0;
     if (done && A.want_true) {
-        X *const to = pb[(k + 1 + A.par) & 1];
+        // x goes out in r's place, which nobody reads any more
         for (int i = tid; i < rows; i += BB) {
             ps[i] = xs[i];
-            publish(to, i, xs[i]);
+            publish(r, i, xs[i]);
         }
         double none[1] = {0};
         if (!meet(none)) return;
-        product(Vec{to, false, (X)0});
+        product(Vec{r, false, (X)0});
         double s[2] = {0, 0};
         for (int i = tid; i < rows; i += BB) {
             const double bi = (double)b[r0 + i], d = bi - (double)qs[i];
@@ -393,6 +476,7 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
     for (int i = tid; i < rows; i += BB) {
         xo[r0 + i] = xs[i];
         if (!(done && A.want_true)) pb[(k + A.par) & 1][r0 + i] = ps[i];
+        if (!done) pb[(k + 1 + A.par) & 1][r0 + i] = rs[i];  // a launch that is given up leaves r overwritten
     }
     if (blockIdx.x == 0 && tid == 0) {
         CgState v;
@@ -411,6 +495,57 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
         v.relres = rel_true;
         A.host[1] = v;
         __threadfence_system();
+    }
+}
+
+// What a workgroup makes of the sums of a meeting, for a solve by steps (one
+// workgroup; the sums are formed as in a meeting).
+template <bool JAC>
+__global__ void __launch_bounds__(BB) k_cgp_scalars(const CgpArgs A, int groups, int phase) {
+    __shared__ double sums[2 * NW];
+    WgSum total{sums};
+    auto grid = [&](int k) { return total((int)threadIdx.x < groups ? A.part[k * PG + threadIdx.x] : 0.0); };
+    CgState *const st = A.st;
+    const bool first = threadIdx.x == 0;
+    if (phase == PHASE_INIT) {
+        const double rho = grid(0), rr = grid(1);
+        if (!first) return;
+        st->rho[0] = rho;
+        st->rho[1] = 0;
+        st->nr0 = sqrt(rr);
+        st->pq = 0;
+        st->relres = rr > 0 ? 1.0 : 0.0;
+        st->tol = A.tol;
+        st->iters = 0;
+        st->maxit = A.maxit;
+        st->done = rr == 0 ? 1 : ((!isfinite(rr) || !isfinite(rho)) ? 3 : (A.maxit <= 0 ? 2 : 0));
+        st->pad = 0;
+        return;
+    }
+    if (phase == PHASE_TRUE) {
+        const double rr = grid(0), bb = grid(1);
+        if (first) A.part[0] = bb > 0 ? sqrt(rr) / sqrt(bb) : sqrt(rr);
+        return;
+    }
+    if (st->done) return;  // (thread 0 writes it after the sums' barriers)
+    const long long k = st->iters;
+    if (phase == PHASE_PQ) {
+        const double pq = grid(2), rho = st->rho[k & 1];
+        if (!first) return;
+        st->iters = k + 1;
+        st->pq = pq;
+        if (!(pq > 0) || !isfinite(pq)) {
+            st->done = 3;
+            st->rho[(k + 1) & 1] = rho;
+        }
+    } else {  // PHASE_RR
+        const double rho1 = grid(0), nr = sqrt(JAC ? grid(1) : rho1), nr0 = st->nr0;
+        if (!first) return;
+        st->relres = nr0 > 0 ? nr / nr0 : 0.0;
+        if (!isfinite(rho1) || !isfinite(nr)) st->done = 3;
+        else if (nr <= st->tol * nr0) st->done = 1;
+        else if (k >= st->maxit) st->done = 2;
+        st->rho[k & 1] = rho1;
     }
 }
 
@@ -504,11 +639,61 @@ static size_t lds_need(int fmt, i64 rpw, i64 win) {
     return w * sizeof(X) + (fmt == DSM_CSR ? sizeof(i32) * (size_t)(rpw + 2) : 0);
 }
 
-template <class V, class X, bool JAC>
+template <class V, class X, bool JAC, bool STEP>
 static const void *kernel_of(int fmt) {
-    if (fmt == DSM_CSR) return (const void *)&k_cg_persist<V, X, DSM_CSR, JAC>;
-    if (fmt == DSM_ELL) return (const void *)&k_cg_persist<V, X, DSM_ELL, JAC>;
-    return (const void *)&k_cg_persist<V, X, DSM_DIA, JAC>;
+    if (fmt == DSM_CSR) return (const void *)&k_cg_persist<V, X, DSM_CSR, JAC, STEP>;
+    if (fmt == DSM_ELL) return (const void *)&k_cg_persist<V, X, DSM_ELL, JAC, STEP>;
+    return (const void *)&k_cg_persist<V, X, DSM_DIA, JAC, STEP>;
+}
+template <class X, bool JAC, bool STEP>
+static const void *kernel_of(int fmt, int vdt) {
+    if constexpr (std::is_same<X, double>::value) {
+        if (vdt == DSM_F64) return kernel_of<double, X, JAC, STEP>(fmt);
+    }
+    return vdt == DSM_F32 ? kernel_of<float, X, JAC, STEP>(fmt) : kernel_of<bf16, X, JAC, STEP>(fmt);
+}
+template <class X, bool STEP>
+static const void *kernel_of(int fmt, int vdt, bool jacobi) {
+    if constexpr (std::is_same<X, double>::value) {
+        if (jacobi) return kernel_of<X, true, STEP>(fmt, vdt);
+    }
+    return kernel_of<X, false, STEP>(fmt, vdt);
+}
+
+// The solve, or what is left of it after the launches that were kept (A.resume;
+// `last`: the state they ended with), by steps; waits.
+template <class X>
+static void cgp_steps(CgpArgs A, const CgState &last, const void *kernel, int groups, size_t lds, CgState *out,
+                      double *rel_true, hipStream_t s) {
+    constexpr int CHUNK = 16;  // iterations between looks at the state
+    const bool jac = A.dinv != nullptr;
+    auto step = [&](int phase) {
+        A.phase = phase;
+        void *args[] = {&A};
+        DSM_HIP(hipLaunchKernel(kernel, dim3(groups), dim3(BB), args, lds, s));
+        if (jac) hipLaunchKernelGGL(k_cgp_scalars<true>, dim3(1), dim3(BB), 0, s, A, groups, phase);
+        else hipLaunchKernelGGL(k_cgp_scalars<false>, dim3(1), dim3(BB), 0, s, A, groups, phase);
+        DSM_HIP(hipGetLastError());
+    };
+    const size_t bytes = sizeof(X) * (size_t)A.n;
+    if (A.resume)
+        DSM_HIP(hipMemcpyAsync(A.r, A.p[(last.iters + 1 + A.par) & 1], bytes, hipMemcpyDeviceToDevice, s));
+    else
+        step(PHASE_INIT);
+    do {
+        for (int i = 0; i < CHUNK; i++) {
+            step(PHASE_PQ);
+            step(PHASE_RR);
+        }
+        DSM_HIP(hipMemcpyAsync(out, A.st, sizeof(CgState), hipMemcpyDeviceToHost, s));
+        DSM_HIP(hipStreamSynchronize(s));
+    } while (!out->done);
+    if (rel_true) {
+        step(PHASE_TRUE);
+        DSM_HIP(hipMemcpyAsync(rel_true, A.part, sizeof(double), hipMemcpyDeviceToHost, s));
+    }
+    DSM_HIP(hipMemcpyAsync(A.x_out, A.x_work, bytes, hipMemcpyDeviceToDevice, s));
+    DSM_HIP(hipStreamSynchronize(s));
 }
 
 template <class X>
@@ -523,10 +708,6 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
     if ((fmt != DSM_CSR && fmt != DSM_DIA && fmt != DSM_ELL) || n < 1 || m->nrows != m->ncols) return false;
     if (fmt == DSM_DIA && (P.ndiag == 0 || P.ndiag > MAX_DIAGS || P.reach < 0)) return false;
     if (m->ctx->device >= MAX_DEVICES) return false;
-    if (cgws.alone_wait > 0) {  // a launch before this one did not get the device
-        cgws.alone_wait--;
-        return false;
-    }
     int ncu = 0;
     DSM_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, m->ctx->device));
     const i64 most = std::min(ncu, PG);
@@ -576,24 +757,19 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
     A.maxit = S.maxit;
     A.x0_zero = S.x0_zero;
     A.want_true = rel_true != nullptr;
+    A.q = S.q;
+    A.part = S.part;
     // iterations per launch: about 20 ms, so that other streams get their turn
     const double us = 8.0 + spmv_bytes(m, P, std::is_same<X, double>::value ? DSM_F64 : DSM_F32) / 5e6;
     A.steps = S.every > 0 ? S.every : (int)std::max(16.0, 20000.0 / us);
-    const void *k;
-    if constexpr (std::is_same<X, double>::value) {
-        if (S.dinv)
-            k = P.vdt == DSM_F64   ? kernel_of<double, X, true>(fmt)
-                : P.vdt == DSM_F32 ? kernel_of<float, X, true>(fmt)
-                                   : kernel_of<bf16, X, true>(fmt);
-        else
-            k = P.vdt == DSM_F64   ? kernel_of<double, X, false>(fmt)
-                : P.vdt == DSM_F32 ? kernel_of<float, X, false>(fmt)
-                                   : kernel_of<bf16, X, false>(fmt);
-    } else {
-        if (P.vdt == DSM_F64) return false;
-        k = P.vdt == DSM_F32 ? kernel_of<float, X, false>(fmt) : kernel_of<bf16, X, false>(fmt);
-    }
-    for (;;) {
+    if (P.vdt == DSM_F64 && !std::is_same<X, double>::value) return false;
+    const void *loop = kernel_of<X, false>(fmt, P.vdt, S.dinv != nullptr);
+    const char *up = getenv("DSM_CG_GIVE_UP");  // the launch of a solve that is given up, for tests
+    const int give_up = up ? atoi(up) : -1;
+    CgState last{};
+    bool by_steps = cgws.alone_wait > 0;  // a solve before this one did not get the device
+    if (by_steps) cgws.alone_wait--;
+    for (int launch = 0; !by_steps; launch++) {
         struct Cus {
             CuShare &share;
             int n;
@@ -601,18 +777,25 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
             ~Cus() { share.give(n); }
         } cus(cu_share[m->ctx->device], G, ncu);
         host[0].done = -1;
-        hipLaunchKernelGGL(k_slots_clear, dim3(SETS * SUMS * PG / 256), dim3(256), 0, s, A.slots, A.outcome);
+        hipLaunchKernelGGL(k_slots_clear, dim3(SETS * SUMS * PG / 256), dim3(256), 0, s, A.slots, A.outcome,
+                           (u32)(launch == give_up ? OUTCOME_GIVEN_UP : OUTCOME_OPEN));
         void *args[] = {&A};
-        DSM_HIP(hipLaunchKernel(k, dim3(G), dim3(BB), args, lds, s));
+        DSM_HIP(hipLaunchKernel(loop, dim3(G), dim3(BB), args, lds, s));
         DSM_HIP(hipStreamSynchronize(s));
-        if (host[0].done < 0) {  // given up; x_in and x_out are as they were
-            cgws.alone_wait = 64;
-            return false;
+        if (host[0].done < 0) {  // given up
+            cgws.alone_wait = ALONE;
+            by_steps = true;
+            break;
         }
-        if (host[0].done) break;
+        last = host[0];
+        if (last.done) break;
         A.resume = 1;
     }
-    *out = host[0];
+    if (by_steps) {
+        cgp_steps<X>(A, last, kernel_of<X, true>(fmt, P.vdt, S.dinv != nullptr), G, lds, out, rel_true, s);
+        return true;
+    }
+    *out = last;
     if (rel_true) *rel_true = host[1].relres;
     return true;
 }

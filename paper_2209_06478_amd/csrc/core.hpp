@@ -132,7 +132,7 @@ struct Workspace {
     // Memory the workspace does not own (the allocation-free entry point's
     // static buffer): ws_get never frees, replaces or grows it.
     bool fixed = false;
-    int alone_wait = 0;  // solves to go before the one-launch CG loop is tried again
+    int alone_wait = 0;  // solves by steps to go before the one-launch CG loop is tried again
 };
 
 }  // namespace dsm
