@@ -138,9 +138,9 @@ __device__ __forceinline__ i64 lanes_hi(i64 n, i64 hi) {
 // 104^3: 11.8 + 6.0 us for x, r and p; now 7.6 + 8.2; FP32 128^3 12.0 + 5.8,
 // now 6.4 + 7.6).  The p update sets the done flag, and a workgroup of the
 // same launch that starts after that store must still do its share of the
-// last x += alpha p: it goes by st->fresh, which the r update of every
-// iteration writes, and derives the end of the loop from the partials like
-// every other workgroup.
+// last x += alpha p: it goes by st->pq, which the r update of every iteration
+// writes (zero past the end), and derives the end of the loop from the partials
+// like every other workgroup.
 //
 // JAC (Jacobi's preconditioner): z = dinv r is formed on the fly, rho is r.z,
 // whose partials go to part_rz.
@@ -173,8 +173,7 @@ __global__ void __launch_bounds__(CGB) k_cg_update_r(i64 n, X *r, const X *q, co
     const bool over = fs.get(lds, &pq);
     const bool breakdown = !(pq > 0) || !isfinite(pq);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->fresh = !over && !breakdown;
-        if (!over) st->pq = pq;
+        st->pq = over ? 0.0 : pq;
         if (!over && breakdown) st->done = 3;
     }
     if (over || breakdown) return;
@@ -238,16 +237,17 @@ __global__ void __launch_bounds__(CGB) k_cg_update_xp(i64 n, X *x, const X *r, X
     };
     // (nrr <= CGG partials)
     FlagSum<CGG / CGB> fs, fz;
-    fs.ask(&st->fresh, part_rr, nrr);
-    if constexpr (JAC) fz.ask(&st->fresh, part_rz, nrr);
+    fs.ask(part_rr, nrr);
+    if constexpr (JAC) fz.ask(part_rz, nrr);
     const long long k = st->iters;
     // this launch writes rho[k & 1] and reads the other
     const double rho = st->rho[(k - 1) & 1], pq = st->pq;
     const double tol = st->tol, nr0 = st->nr0;
     const long long maxit = st->maxit;
     load();
-    double rr, rho1;
-    if (!fs.get(lds, &rr)) return;
+    const double rr = fs.total(lds);
+    double rho1;
+    if (!(pq > 0) || !isfinite(pq)) return;
     if constexpr (JAC) rho1 = fz.total(lds);
     else rho1 = rr;
     const double nr = sqrt(rr);
@@ -606,7 +606,6 @@ struct CgBuffers {
     double *xw = nullptr;
     double *part_a = nullptr, *part_b = nullptr, *norms = nullptr;
     CgState *st = nullptr, *st2 = nullptr;
-    void *meet = nullptr;  // scratch of the one-launch loop
     // FP32 inner part (IR)
     float *r32 = nullptr, *p32 = nullptr, *q32 = nullptr, *d32 = nullptr, *ri32 = nullptr, *p32b = nullptr;
 };
@@ -623,7 +622,6 @@ size_t cg_workspace_bytes(i64 n, bool ir) {
     const size_t nn = (size_t)std::max<i64>(n, 1);
     size_t bytes = 6 * round256(nn * 8) + 3 * round256(partial_slots(n) * 8) + 8 * 256;
     if (ir) bytes += 6 * round256(nn * 4);
-    bytes += round256(cg_persist_bytes());
     return bytes;
 }
 
@@ -648,7 +646,6 @@ static CgBuffers cg_buffers(dsm_matrix m, bool ir, Workspace &cgws, hipStream_t 
     B.norms = (double *)take(64);
     B.st = (CgState *)take(sizeof(CgState));
     B.st2 = (CgState *)take(sizeof(CgState));
-    B.meet = take(cg_persist_bytes());
     if (ir) {
         B.r32 = (float *)take(n * 4);
         B.p32 = (float *)take(n * 4);
@@ -864,7 +861,7 @@ void cg_solve_ws(dsm_matrix m, const double *b, double *x, const dsm_cg_opts &o,
     if (o.mode == DSM_CG_JACOBI) {
         jacobi_dinv(m, B, s);
         CgState h;
-        const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, B.dinv, B.meet, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every};
+        const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, B.dinv, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every};
         if (use_graph && cg_persist<double>(m, S, s, cgws, &h, &R.relres_true)) {
             finish(h);
             return;
@@ -886,7 +883,7 @@ void cg_solve_ws(dsm_matrix m, const double *b, double *x, const dsm_cg_opts &o,
         // passes (with the caller's x in it, a new x meant a new capture).
         CgState h;
         if (use_graph && !fused_ok(m)) {
-            const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, nullptr, B.meet, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every};
+            const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, nullptr, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every};
             if (cg_persist<double>(m, S, s, cgws, &h, &R.relres_true)) {
                 finish(h);
                 return;
@@ -972,7 +969,7 @@ void cg_solve_ws(dsm_matrix m, const double *b, double *x, const dsm_cg_opts &o,
         const long long left = std::max<long long>(1, maxit - inner_total);
         CgState h;
         const CgpSolve<float> S{B.r32, nullptr, B.d32, B.q32, {B.p32, B.p32b}, B.ri32, (float *)B.q, last_p, nullptr,
-                                B.meet, B.part_a, B.st2, tau, pc, left, true, o.check_every};
+                                B.part_a, B.st2, tau, pc, left, true, o.check_every};
         if (use_graph && !fused_ok(m) && cg_persist<float>(m, S, s, cgws, &h, nullptr)) {
             last_p = (int)((h.iters + last_p) & 1);
         } else {

@@ -18,14 +18,13 @@ constexpr int CGG = 512;    // workgroups in the vector kernels (= partials)
 struct CgState {
     double rho[2];   // r.r (r.z when preconditioned) before iteration k is rho[(k-1) & 1]
     double nr0;      // ||r0||
-    double pq;
+    double pq;       // p.q of the iteration; not positive and finite: its x is not to be updated
     double relres;
     double tol;
     long long iters; // SpMVs done inside the loop
     long long maxit;
     int done;        // 0 running, 1 converged, 2 iteration limit, 3 breakdown
     int pad;         // sequence number of the state copies to the host
-    int fresh;       // the iteration's r update ran: its x is still to be updated
 };
 
 // Contiguous slice [slice_lo(n), slice_hi(n)) of [0, n) for this workgroup,
@@ -71,9 +70,12 @@ struct FlagSum {
     int count, flag;
     double w[PB];
     __device__ __forceinline__ void ask(const int *f, const double *p, int n) {
+        flag = *f;  // thread 0's counts: a launch may write the flag while it runs
+        ask(p, n);
+    }
+    __device__ __forceinline__ void ask(const double *p, int n) {
         part = p;
         count = n;
-        flag = *f;  // thread 0's counts: a launch may write the flag while it runs
         take(0);
     }
     __device__ __forceinline__ void take(int base) {
@@ -110,8 +112,8 @@ struct FlagSum {
 bool cg_graphs_enabled();
 
 // A solve by the one-launch loop (cg_persist.hip): b, x and the work vectors
-// p, r, q, x_work of one type; `meet` holds cg_persist_bytes() of scratch, part
-// 768 doubles.
+// p, r, q, x_work of one type; q (n doubles whatever the type) also holds the
+// words of the workgroups' meetings, part 768 doubles.
 template <class X>
 struct CgpSolve {
     const X *b, *x_in;
@@ -119,7 +121,6 @@ struct CgpSolve {
     int par;             // the direction of iteration k ends in p[(k + par) & 1]; pcont != 0:
                          // the direction to continue is in p[par & 1]
     const double *dinv;  // Jacobi's inverse diagonal, or null
-    void *meet;
     double *part;
     CgState *st;
     double tol, pcont;
@@ -127,7 +128,6 @@ struct CgpSolve {
     bool x0_zero;  // x_in is zero (and not read)
     int every;     // iterations per launch; <= 0: chosen by size
 };
-size_t cg_persist_bytes();
 // Solves and waits; false, with nothing done, when the system does not fit that
 // loop.  The solves in flight on a device share its CUs (a solve waits for its
 // turn); one whose launch could not be held at once all the same goes on step by

@@ -25,7 +25,8 @@
 // everyone has finished reading the set two before.  Words and r are stored
 // and loaded past the L2s, which are not coherent between XCDs within a
 // launch; each wave waits for its stores before its workgroup's word goes
-// out.  Measured alone: 2.4 us over 8 workgroups, 4.5 us over 256 (an
+// out.  The words lie in the memory of q, which the launch keeps in LDS.
+// Measured alone: 2.4 us over 8 workgroups, 4.5 us over 256 (an
 // agent-scope fence per wave instead of the plain stores past the L2: 38 us).
 //
 // Whole solves to 1e-10, launch-per-step loop -> now: HPCG 16^3 CSR 774 -> 340
@@ -116,9 +117,9 @@ __device__ __forceinline__ void st_agent(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void k_slots_clear(u64 *slots, u32 *outcome, u32 open) {
+__global__ void k_slots_clear(u64 *slots, int n, u32 *outcome, u32 open) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < SETS * SUMS * PG) slots[i] = EMPTY;
+    if (i < n) slots[i] = EMPTY;
     if (i == 0) *outcome = open;
 }
 
@@ -148,24 +149,25 @@ struct Meeting {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int k = 0; k < N; k++) v[k] = total(v[k]);
-        u64 *now = slots + (size_t)set * SUMS * PG, *clear = slots + (size_t)((set + 2) % SETS) * SUMS * PG;
+        const u32 G = gridDim.x;
+        u64 *now = slots + (size_t)set * SUMS * G, *clear = slots + (size_t)((set + 2) % SETS) * SUMS * G;
         if (threadIdx.x == 0) {
 #pragma unroll
             for (int k = 0; k < N; k++)
-                st_agent(now + k * PG + blockIdx.x, v[k] == v[k] ? __builtin_bit_cast(u64, v[k]) : NAN_WORD);
+                st_agent(now + k * G + blockIdx.x, v[k] == v[k] ? __builtin_bit_cast(u64, v[k]) : NAN_WORD);
 #pragma unroll
-            for (int k = 0; k < SUMS; k++) st_agent(clear + k * PG + blockIdx.x, EMPTY);
+            for (int k = 0; k < SUMS; k++) st_agent(clear + k * G + blockIdx.x, EMPTY);
         }
         u64 w[N];
 #pragma unroll
         for (int k = 0; k < N; k++) w[k] = 0;
-        if (threadIdx.x < gridDim.x) {
+        if (threadIdx.x < G) {
             const long long t0 = wall_clock64();
             for (u32 tries = 1;; tries++) {
                 bool all = true;
 #pragma unroll
                 for (int k = 0; k < N; k++) {
-                    w[k] = ld_agent(now + k * PG + threadIdx.x);
+                    w[k] = ld_agent(now + k * G + threadIdx.x);
                     all = all && w[k] != EMPTY;
                 }
                 if (all) break;
@@ -579,25 +581,20 @@ __global__ void __launch_bounds__(256) k_reach_ell(i64 n, i64 K, i64 pitch, cons
     if (threadIdx.x == 0 && m > 0) atomicMax(out, m);
 }
 
-static i64 reach_of(dsm_matrix m, hipStream_t s) {
+// d: an int of scratch
+static i64 reach_of(dsm_matrix m, int *d, hipStream_t s) {
     Payload &P = m->P;
     if (P.reach >= 0) return P.reach;
-    int *d = (int *)dev_alloc(m->ctx, sizeof(int), s), h = 0;
-    try {
-        DSM_HIP(hipMemsetAsync(d, 0, sizeof(int), s));
-        const unsigned g = std::min<unsigned>(512, grid_for(m->nrows, 256));
-        if (P.fmt == DSM_CSR)
-            hipLaunchKernelGGL(k_reach_csr, dim3(g), dim3(256), 0, s, m->nrows, P.rp, P.col, d);
-        else
-            hipLaunchKernelGGL(k_reach_ell, dim3(g), dim3(256), 0, s, m->nrows, P.K, P.pitch, P.ecol, d);
-        DSM_HIP(hipGetLastError());
-        DSM_HIP(hipMemcpyAsync(&h, d, sizeof(int), hipMemcpyDeviceToHost, s));
-        DSM_HIP(hipStreamSynchronize(s));
-    } catch (...) {
-        dev_free(m->ctx, d, sizeof(int));
-        throw;
-    }
-    dev_free(m->ctx, d, sizeof(int), s);
+    int h = 0;
+    DSM_HIP(hipMemsetAsync(d, 0, sizeof(int), s));
+    const unsigned g = std::min<unsigned>(512, grid_for(m->nrows, 256));
+    if (P.fmt == DSM_CSR)
+        hipLaunchKernelGGL(k_reach_csr, dim3(g), dim3(256), 0, s, m->nrows, P.rp, P.col, d);
+    else
+        hipLaunchKernelGGL(k_reach_ell, dim3(g), dim3(256), 0, s, m->nrows, P.K, P.pitch, P.ecol, d);
+    DSM_HIP(hipGetLastError());
+    DSM_HIP(hipMemcpyAsync(&h, d, sizeof(int), hipMemcpyDeviceToHost, s));
+    DSM_HIP(hipStreamSynchronize(s));
     return P.reach = h;
 }
 
@@ -629,8 +626,6 @@ constexpr int MAX_DEVICES = 64;
 static CuShare cu_share[MAX_DEVICES];
 
 constexpr size_t LDS_MAX = (160 << 10) - 1024 - sizeof(i32) * MAX_DIAGS;
-
-size_t cg_persist_bytes() { return sizeof(u64) * SETS * SUMS * PG + 256; }
 
 template <class X>
 static size_t lds_need(int fmt, i64 rpw, i64 win) {
@@ -717,7 +712,7 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
     const i64 rpw = (std::max<i64>(PROWS, (n + most - 1) / most) + 63) / 64 * 64;
     const int G = (int)((n + rpw - 1) / rpw);
     if (lds_need<X>(fmt, rpw, 0) > LDS_MAX) return false;
-    const i64 win = std::min<i64>(fmt == DSM_DIA ? P.reach : reach_of(m, s), n);
+    const i64 win = std::min<i64>(fmt == DSM_DIA ? P.reach : reach_of(m, (int *)S.part, s), n);
     const size_t lds = lds_need<X>(fmt, rpw, win);
     if (lds > LDS_MAX) return false;
     if (!cgws.host)
@@ -748,8 +743,10 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
     A.par = S.par;
     A.r = S.r;
     A.dinv = S.dinv;
-    A.slots = (u64 *)S.meet;
-    A.outcome = (u32 *)(A.slots + SETS * SUMS * PG);
+    // 64 G + 4 bytes of the 8 n, rounded up to 256: n > 256 (G - 1)
+    static_assert(sizeof(u64) * SETS * SUMS < 8 * PROWS, "the words of the meetings lie in q");
+    A.slots = (u64 *)S.q;
+    A.outcome = (u32 *)(A.slots + SETS * SUMS * G);
     A.st = S.st;
     A.host = host_dev;
     A.tol = S.tol;
@@ -777,7 +774,8 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
             ~Cus() { share.give(n); }
         } cus(cu_share[m->ctx->device], G, ncu);
         host[0].done = -1;
-        hipLaunchKernelGGL(k_slots_clear, dim3(SETS * SUMS * PG / 256), dim3(256), 0, s, A.slots, A.outcome,
+        hipLaunchKernelGGL(k_slots_clear, dim3(grid_for(SETS * SUMS * G, 256)), dim3(256), 0, s, A.slots,
+                           SETS * SUMS * G, A.outcome,
                            (u32)(launch == give_up ? OUTCOME_GIVEN_UP : OUTCOME_OPEN));
         void *args[] = {&A};
         DSM_HIP(hipLaunchKernel(loop, dim3(G), dim3(BB), args, lds, s));
