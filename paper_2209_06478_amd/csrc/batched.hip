@@ -62,24 +62,25 @@ struct BRes {
 // instructions per stored slot (4 cycles each per wave and SIMD).  So loads
 // are issued in batches whose addresses are a scalar base plus one offset
 // per lane, bounds tests sit on whole batches, and padding columns (-1) read
-// the zero word kept just below p[0].  Measured per iteration, before (512
+// the zero word kept just below p[0] in LDS.  Measured per iteration, before (512
 // threads; a chain of dependent round trips per 512 / lanes rows, p and all
 // else through the L2) and now: 4096 rows, CSR SPD band of 39 entries a row
 // 336 -> 47-57 us, HPCG 16^3 CSR 337 -> 32-39 us, ELL 42 -> 26 us, DIA 50 ->
 // 28 us; HPCG 24^3 ELL 156 -> 95 us; HPCG 8^3 ELL 7.4 -> 5.6 us.  128 systems
 // of up to 4096 rows in one call: 17.6 -> 2.0 ms.
-// q = A p for one descriptor, the zero word at p[-1]
+// q = A p for one descriptor, the zero word at p[zero]
 template <class PP, class QQ, class RPP>
-__device__ __forceinline__ void csr_spmv(const BReq &R, const WaveRows &rows, PP p, QQ q, RPP rp, double *prod) {
-    wg_spmv_csr(rows, R.lanes, R.col, R.val, p, -1, q, rp, prod);
+__device__ __forceinline__ void csr_spmv(const BReq &R, const WaveRows &rows, PP p, int zero, QQ q, RPP rp,
+                                         double *prod) {
+    wg_spmv_csr(rows, R.lanes, R.col, R.val, p, zero, q, rp, prod);
 }
 template <int U, int B, class PP, class QQ>
-__device__ __forceinline__ void dia_spmv(const BReq &R, PP p, QQ q) {
-    wg_spmv_dia<double, U, B>((int)R.n, 0, (int)R.n, (int)R.ndiag, R.pitch, R.offs, R.dval, p, -1, q);
+__device__ __forceinline__ void dia_spmv(const BReq &R, PP p, int zero, QQ q) {
+    wg_spmv_dia<double, U, B>((int)R.n, 0, (int)R.n, (int)R.ndiag, R.pitch, R.offs, R.dval, p, zero, q);
 }
-template <int U, int B, class PP, class QQ>
-__device__ __forceinline__ void ell_spmv(const BReq &R, PP p, QQ q) {
-    wg_spmv_ell<double, U, B, true>((int)R.n, (int)R.K, (int)R.pitch, R.ecol, R.evl, p, -1, q);
+template <int U, int B, bool ZERO_BELOW, class PP, class QQ>
+__device__ __forceinline__ void ell_spmv(const BReq &R, PP p, int zero, QQ q) {
+    wg_spmv_ell<double, U, B, ZERO_BELOW>((int)R.n, (int)R.K, (int)R.pitch, R.ecol, R.evl, p, zero, q);
 }
 
 // ---- where a system's vectors live
@@ -87,7 +88,8 @@ __device__ __forceinline__ void ell_spmv(const BReq &R, PP p, QQ q) {
 // the row pointers in LDS, and q in LDS where it still fits; an iteration
 // then reads nothing from memory but the matrix, x and r (x and r stay in
 // memory: held in registers, they cost the products 70-120 spilled ones).
-// Larger systems keep all vectors in memory (p has its zero word there too).
+// Larger systems keep all vectors in memory, and share a zero word in the
+// arena's fixed part.
 constexpr i64 WL_ROWS = 19000;       // 8 bytes a row
 constexpr i64 WL_Q_ROWS = 9500;      // q in LDS too: 16 bytes a row
 constexpr i64 WL_CSR_ROWS = 8000;    // 12 bytes a row beside the 64 KB of products
@@ -107,8 +109,10 @@ static __host__ __device__ size_t lds_bytes(int fmt, i64 n) {
 // One system, start to end.  ONCU: p on the CU as above.  A solve is a
 // sequence of products q = A p: the first with x0 in p's place, the last
 // with the final x (for the true residual).
+// zero_word: the zero word of the other systems.
 template <bool ONCU>
-__device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *lds, char *dyn) {
+__device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *lds, char *dyn,
+                                          const double *zero_word) {
     const BReq &R = *req;
     const int tid = threadIdx.x;
     const int n = (int)R.n;
@@ -128,7 +132,7 @@ __device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *ld
         if (ONCU && ql) return qs[i];
         return R.q[i];
     };
-    if (tid == 0) setp(-1, 0.0);
+    if (ONCU && tid == 0) ps[-1] = 0.0;
     if (ONCU && R.fmt == DSM_CSR)
         for (int i = tid; i <= n; i += BB) rps[i] = R.rp[i];
     for (int i = tid; i < n; i += BB) setp(i, R.x[i]);
@@ -155,20 +159,21 @@ __device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *ld
         const BReq *again = req;
         asm volatile("" : "+s"(again));
         const BReq &R = *again;
+        const int zero = ONCU ? -1 : (int)(zero_word - R.p);
         if (R.fmt == DSM_CSR) {
-            if (ONCU && ql) csr_spmv(R, wrows, ps, qs, rps, prod);
-            else if (ONCU) csr_spmv(R, wrows, ps, R.q, rps, prod);
-            else csr_spmv(R, wrows, R.p, R.q, R.rp, prod);
+            if (ONCU && ql) csr_spmv(R, wrows, ps, zero, qs, rps, prod);
+            else if (ONCU) csr_spmv(R, wrows, ps, zero, R.q, rps, prod);
+            else csr_spmv(R, wrows, R.p, zero, R.q, R.rp, prod);
         } else if (R.fmt == DSM_DIA) {
-            if (ONCU && n <= BB) dia_spmv<1, 16>(R, ps, qs);
-            else if (ONCU && ql) dia_spmv<2, 8>(R, ps, qs);
-            else if (ONCU) dia_spmv<2, 8>(R, ps, R.q);
-            else dia_spmv<2, 8>(R, R.p, R.q);
+            if (ONCU && n <= BB) dia_spmv<1, 16>(R, ps, zero, qs);
+            else if (ONCU && ql) dia_spmv<2, 8>(R, ps, zero, qs);
+            else if (ONCU) dia_spmv<2, 8>(R, ps, zero, R.q);
+            else dia_spmv<2, 8>(R, R.p, zero, R.q);
         } else {
-            if (ONCU && n <= BB) ell_spmv<1, 16>(R, ps, qs);
-            else if (ONCU && ql) ell_spmv<2, 8>(R, ps, qs);
-            else if (ONCU) ell_spmv<2, 8>(R, ps, R.q);
-            else ell_spmv<2, 8>(R, R.p, R.q);
+            if (ONCU && n <= BB) ell_spmv<1, 16, true>(R, ps, zero, qs);
+            else if (ONCU && ql) ell_spmv<2, 8, true>(R, ps, zero, qs);
+            else if (ONCU) ell_spmv<2, 8, true>(R, ps, zero, R.q);
+            else ell_spmv<2, 8, false>(R, R.p, zero, R.q);
         }
         if (R.fmt == DSM_CSR) __syncthreads();  // DIA and ELL: a thread reads its own q only
         double a = 0, c = 0;
@@ -247,7 +252,7 @@ __device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *ld
 }
 
 __global__ void __launch_bounds__(BB) k_cg_batched(const BReq *__restrict__ reqs, BRes *__restrict__ res, int count,
-                                                   int *next) {
+                                                   int *next, const double *zero_word) {
     __shared__ double lds[2 * NW];
     __shared__ int sidx;
     extern __shared__ char dyn[];  // lds_bytes of the launch's largest system
@@ -259,8 +264,8 @@ __global__ void __launch_bounds__(BB) k_cg_batched(const BReq *__restrict__ reqs
         __syncthreads();
         if (idx >= count) return;
         const BReq *req = reqs + idx;
-        if (on_cu(req->fmt, req->n)) solve_one<true>(req, &res[idx], lds, dyn);
-        else solve_one<false>(req, &res[idx], lds, dyn);
+        if (on_cu(req->fmt, req->n)) solve_one<true>(req, &res[idx], lds, dyn, zero_word);
+        else solve_one<false>(req, &res[idx], lds, dyn, zero_word);
     }
 }
 
@@ -283,11 +288,10 @@ static int default_lanes(const dsm_matrix_s *m, const Payload &P) {
 
 static size_t vec_bytes(i64 n) { return ((size_t)std::max<i64>(n, 1) * 8 + 255) & ~(size_t)255; }
 
-// Arena bytes of one batch: a fixed part (the work counter and the 256-byte
-// rounding of the descriptor and result arrays) plus one share per request.
-// p has room for its zero word below it.
-constexpr size_t P_PAD = 256;
-size_t batch_request_bytes(i64 n) { return 3 * vec_bytes(n) + P_PAD + sizeof(BReq) + sizeof(BRes); }
+// Arena bytes of one batch: a fixed part (the work counter, the zero word and
+// the 256-byte rounding of the descriptor and result arrays) plus one share per
+// request.
+size_t batch_request_bytes(i64 n) { return 3 * vec_bytes(n) + sizeof(BReq) + sizeof(BRes); }
 size_t batch_arena_fixed() { return 1536; }
 
 static BReq make_req(const dsm_matrix_s *m, const Payload &P, int lanes) {
@@ -322,23 +326,25 @@ static void launch_reqs(dsm_ctx ctx, std::vector<BReq> &hreq, std::vector<BRes> 
         base += (sz + 255) & ~(size_t)255;
         return (void *)p;
     };
-    int *next = (int *)take(sizeof(int));
+    int *next = (int *)take(2 * sizeof(double));
+    double *zero_word = (double *)next + 1;
     BReq *dreq = (BReq *)take(sizeof(BReq) * count);
     BRes *dres = (BRes *)take(sizeof(BRes) * count);
     for (auto &R : hreq) {
         R.r = (double *)take(vec_bytes(R.n));
-        R.p = (double *)((char *)take(vec_bytes(R.n) + P_PAD) + P_PAD);
+        R.p = (double *)take(vec_bytes(R.n));
         R.q = (double *)take(vec_bytes(R.n));
     }
     hres.resize(count);
     DSM_HIP(hipMemcpyAsync(dreq, hreq.data(), sizeof(BReq) * count, hipMemcpyHostToDevice, s));
-    DSM_HIP(hipMemsetAsync(next, 0, sizeof(int), s));
+    DSM_HIP(hipMemsetAsync(next, 0, 2 * sizeof(double), s));
     int ncu = 256;
     DSM_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, ctx->device));
     const unsigned grid = (unsigned)std::min(count, ncu * 4);
     size_t dyn = 0;
     for (auto &R : hreq) dyn = std::max(dyn, lds_bytes(R.fmt, R.n));
-    hipLaunchKernelGGL(k_cg_batched, dim3(grid), dim3(BB), dyn, s, dreq, dres, count, next);
+    hipLaunchKernelGGL(k_cg_batched, dim3(grid), dim3(BB), dyn, s, dreq, dres, count, next,
+                       zero_word);
     DSM_HIP(hipGetLastError());
     DSM_HIP(hipMemcpyAsync(hres.data(), dres, sizeof(BRes) * count, hipMemcpyDeviceToHost, s));
     DSM_HIP(hipStreamSynchronize(s));

@@ -44,3 +44,31 @@ def test_cg_workspace(n):
     assert c.bytes_in_use() == csr + need
     A.close()
     c.close()
+
+
+def test_batch_arena():
+    """Three FP64 vectors a system, 184 bytes for its descriptor and result, 1536 for the batch: systems
+    whose vectors lie in LDS and in memory (beyond 8000 rows in CSR, 19000 in DIA and ELL)."""
+    torch, dev = torch_dev()
+    # (the conversions first: they need room for both formats)
+    probs = [(inputs.banded_spd(n, 4, seed=n), f) for n, f in
+             [(32000, "dia"), (20480, "ell"), (1024, "dia"), (96, "ell"), (9984, "csr"), (7936, "csr"), (1, "csr")]]
+
+    def solve(budget):
+        c = dsm.Context(0, hbm_budget=budget)
+        mats = [dsm.Matrix.from_csr(c, p.nrows, p.ncols, p.row_ptr, p.col, p.val).convert(f) for p, f in probs]
+        held = c.bytes_in_use()
+        xs = [torch.zeros(p.nrows, dtype=torch.float64, device=dev) for p, _ in probs]
+        res = dsm.cg_batched(mats, [torch.from_numpy(p.b).to(dev) for p, _ in probs], xs, tol=1e-9)
+        for A in mats:
+            A.close()
+        c.close()
+        return held, xs, res
+
+    held, xs, res = solve(0)
+    for (p, f), x, r in zip(probs, xs, res):
+        assert r["status"] == "converged"
+        assert oracle.true_relres(p.row_ptr, p.col, p.val, p.b, x.cpu().numpy()) <= 1.5e-9
+    need = 1536 + sum(3 * r256(8 * p.nrows) + 184 for p, _ in probs)
+    _, ys, qs = solve(held + need)
+    assert qs == res and all(torch.equal(x, y) for x, y in zip(xs, ys))
