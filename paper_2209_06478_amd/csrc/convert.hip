@@ -189,7 +189,6 @@ __global__ void k_rowblock_flags(i64 nrows, const i32 *rp, i32 *flag) {
     i64 i = (i64)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nrows) return;
     int f = 1;
-    if (i == 0) flag[nrows] = 0;  // counter of k_heavy_rows
     if (i > 0) {
         i32 a = rp[i - 1], b = rp[i], c = rp[i + 1];
         f = (b / RB_T != a / RB_T) || (b - a > RB_T) || (c - b > RB_T) || (i % RB_RCAP == 0);
@@ -197,10 +196,15 @@ __global__ void k_rowblock_flags(i64 nrows, const i32 *rp, i32 *flag) {
     flag[i] = f;
 }
 
-__global__ void k_rowblock_scatter(i64 nrows, const i32 *flag, const i32 *pos, i32 *blocks, i64 nblocks) {
+// pos[nrows], the number of blocks, has been read: it becomes k_heavy_rows'
+// counter.
+__global__ void k_rowblock_scatter(i64 nrows, const i32 *flag, i32 *pos, i32 *blocks, i64 nblocks) {
     i64 i = (i64)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nrows && flag[i]) blocks[pos[i]] = (i32)i;
-    if (i == 0) blocks[nblocks] = (i32)nrows;
+    if (i == 0) {
+        blocks[nblocks] = (i32)nrows;
+        pos[nrows] = 0;
+    }
 }
 
 // Entries of rows of more than 32 and four times the mean.  A few workgroups,
@@ -224,14 +228,14 @@ void build_row_blocks(dsm_ctx ctx, Payload &P, i64 nrows, hipStream_t s) {
         DSM_HIP(hipMemsetAsync(P.rblocks, 0, sizeof(i32), s));
         return;
     }
-    Tmp flag(ctx, sizeof(i32) * (size_t)(nrows + 1), s), pos(ctx, sizeof(i32) * (size_t)(nrows + 1), s);
+    Tmp flag(ctx, sizeof(i32) * (size_t)nrows, s), pos(ctx, sizeof(i32) * (size_t)(nrows + 1), s);
     hipLaunchKernelGGL(k_rowblock_flags, dim3(grid_for(nrows, CB)), dim3(CB), 0, s, nrows, P.rp, flag.as<i32>());
     DSM_HIP(hipGetLastError());
     i64 nb = exclusive_scan_i32(ctx, flag.as<i32>(), pos.as<i32>(), nrows, s, true);
     P.nrblocks = nb;
     P.rblocks = (i32 *)P.alloc(ctx, sizeof(i32) * (size_t)(nb + 1));
     const bool big = nb >= 4096;
-    i32 *heavy = flag.as<i32>() + nrows, h = 0;
+    i32 *heavy = pos.as<i32>() + nrows, h = 0;
     hipLaunchKernelGGL(k_rowblock_scatter, dim3(grid_for(nrows, CB)), dim3(CB), 0, s, nrows, flag.as<i32>(),
                        pos.as<i32>(), P.rblocks, nb);
     if (big) hipLaunchKernelGGL(k_heavy_rows, dim3(256), dim3(CB), 0, s, nrows, P.rp, heavy);
@@ -956,9 +960,11 @@ static Payload from_csr_typed(dsm_matrix m, const Payload &C, int fmt, const dsm
                 if (n > 0 && nco > 0)
                     hipLaunchKernelGGL((k_overflow_fill<W>), dim3(grid_for(n, CB)), dim3(CB), 0, s, n, C.rp,
                                        C.col, (const W *)C.val, K, orp.as<i32>(), P.crow, P.ccol, (W *)P.cval);
-                if (n > 0 && nco > 0 && longest >= 0) {
-                    const i64 nblk = (n + 255) / 256;
-                    P.cblk = (i32 *)P.alloc(ctx, sizeof(i32) * (size_t)(nblk + 1));
+                // (memory that only makes products faster is none of a budget's)
+                const i64 nblk = (n + 255) / 256;
+                if (n > 0 && nco > 0 && longest >= 0 && !ctx->budget)
+                    P.cblk = (i32 *)P.try_alloc(ctx, sizeof(i32) * (size_t)(nblk + 1));
+                if (P.cblk) {
                     P.coo_row_max = longest - K;
                     hipLaunchKernelGGL(k_overflow_blocks, dim3(grid_for(nblk + 1, CB)), dim3(CB), 0, s, n, nblk,
                                        orp.as<i32>(), P.cblk);

@@ -70,7 +70,7 @@ struct Payload {
     i32 *crow = nullptr, *ccol = nullptr;
     void *cval = nullptr;
     i64 coo_nnz = 0;
-    i32 *cblk = nullptr;      // HYB: first overflow entry of each group of 256 rows, and their number
+    i32 *cblk = nullptr;      // HYB: first overflow entry of each group of 256 rows, and their number (null under a budget)
     i64 coo_row_max = 1LL << 40;  // HYB: most overflow entries of a row (where cblk is set)
     // DIA (HDC)
     i32 *offs = nullptr;
@@ -103,6 +103,15 @@ struct Payload {
         bufs.push_back({p, b});
         bytes += b;
         return p;
+    }
+    // null where there is no room
+    void *try_alloc(dsm_ctx ctx, size_t b) {
+        try {
+            return alloc(ctx, b);
+        } catch (const Error &) {
+            clear_error();
+            return nullptr;
+        }
     }
     void release(dsm_ctx ctx, bool unused = false) {
         for (auto &pb : bufs) dev_free(ctx, pb.first, pb.second, any_stream(), unused);

@@ -72,3 +72,32 @@ def test_batch_arena():
     need = 1536 + sum(3 * r256(8 * p.nrows) + 184 for p, _ in probs)
     _, ys, qs = solve(held + need)
     assert qs == res and all(torch.equal(x, y) for x, y in zip(xs, ys))
+
+
+@pytest.mark.parametrize("name", ["zipf", "spd"])
+def test_creation_and_hyb(name):
+    """A matrix fits in its row pointers, entries and row blocks, with its flags and their prefix sums
+    during creation; HYB holds its ELL slots and overflow entries only.  Products are as close without the
+    overflow's row groups."""
+    torch, dev = torch_dev()
+    p = inputs.zipf(nrows=50000, seed=5) if name == "zipf" else inputs.banded_spd(20000, 5, seed=1)
+    n, nnz = p.nrows, p.col.size
+    csr, hyb = payload_bytes(p, "hyb")
+    c = dsm.Context(0, hbm_budget=csr + 4 * (2 * n + 1) + 16 * (2 * (n // 4096 + 1) + 1))
+    A = dsm.Matrix.from_csr(c, p.nrows, p.ncols, p.row_ptr, p.col, p.val)
+    assert c.bytes_in_use() == csr
+    A.close()
+    c.close()
+    c = dsm.Context(0, hbm_budget=1 << 30)
+    A = dsm.Matrix.from_csr(c, p.nrows, p.ncols, p.row_ptr, p.col, p.val)
+    A.convert("hyb")
+    i = A.info()
+    slots = i["ell_width"] * i["pitch"]
+    assert c.bytes_in_use() == i["bytes"] == max(4 * slots, 16) + max(8 * slots, 16) + 2 * max(4 * i["coo_nnz"], 16) + max(
+        8 * i["coo_nnz"], 16)
+    x = np.cos(np.arange(p.ncols))
+    yref, scale = oracle.spmv_csr_ref(p.row_ptr, p.col, p.val, x)
+    y = A.spmv(torch.from_numpy(x).to(dev)).cpu().numpy()
+    assert np.max(np.abs(y - yref) / np.maximum(scale, 1e-300)) <= 1e-14
+    A.close()
+    c.close()
