@@ -70,6 +70,7 @@ struct dsm_mg_s {
         dsm::Workspace spws;
     };
     dsm_ctx ctx = nullptr;
+    bool extras = true;  // memory that only makes the cycle faster is there: parted levels' tables and sums, `first`
     std::vector<Level> L;
     std::vector<std::pair<void *, size_t>> bufs;
     // PCG vectors and state (xw: the iterate of the graph-replayed loop)
@@ -1051,19 +1052,21 @@ static void build_level(dsm_mg_s *mg, int l, dsm_matrix A, const int32_t *colour
     lv.diag = (double *)mg->alloc(sizeof(double) * (size_t)std::max<i64>(n, 1));
     int32_t *col_d = (int32_t *)dev_alloc(mg->ctx, sizeof(int32_t) * (size_t)std::max<i64>(n, 1));
     constexpr int MAX_COLOURS = 256;
-    constexpr size_t NBAD = 2 + 2 * MAX_COLOURS;  // error counts, then the sides of k_colour_check_dia
-    int *bad = (int *)dev_alloc(mg->ctx, NBAD * sizeof(int));
+    const bool parts = mg->extras && n >= PART_ROWS && lv.fmt == DSM_DIA && (A->P.ndiag == 7 || A->P.ndiag == 27);
+    int hb[2 + 2 * MAX_COLOURS] = {};  // error counts, then the sides of k_colour_check_dia
+    const size_t hb_bytes = parts ? sizeof(hb) : 2 * sizeof(int);
+    int *bad = nullptr;
     auto cleanup = [&] {
         (void)hipStreamSynchronize(s);
         dev_free(mg->ctx, col_d, sizeof(int32_t) * (size_t)std::max<i64>(n, 1));
-        dev_free(mg->ctx, bad, NBAD * sizeof(int));
+        dev_free(mg->ctx, bad, hb_bytes);
     };
-    int hb[NBAD] = {};
     try {
+        bad = (int *)dev_alloc(mg->ctx, hb_bytes);
         DSM_HIP(hipMemcpyAsync(lv.rows, rows.data(), sizeof(int32_t) * rows.size(), hipMemcpyHostToDevice, s));
         if (n > 0)
             DSM_HIP(hipMemcpyAsync(col_d, colour_h, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, s));
-        DSM_HIP(hipMemsetAsync(bad, 0, NBAD * sizeof(int), s));
+        DSM_HIP(hipMemsetAsync(bad, 0, hb_bytes, s));
         diagonal_op(A, lv.diag, 0, s);
         if (n > 0) {
             const Payload &P = A->P;
@@ -1072,12 +1075,11 @@ static void build_level(dsm_mg_s *mg, int l, dsm_matrix A, const int32_t *colour
                                    bad);
             else
                 hipLaunchKernelGGL(k_colour_check_dia, dim3(grid_for(n, MB)), dim3(MB), 0, s, n, P.ndiag, P.offs,
-                                   (const double *)P.dval, P.pitch, col_d, bad,
-                                   P.ndiag == 7 || P.ndiag == 27 ? (u32 *)bad + 2 : nullptr);
+                                   (const double *)P.dval, P.pitch, col_d, bad, parts ? (u32 *)bad + 2 : nullptr);
             hipLaunchKernelGGL(k_count_bad_diag, dim3(grid_for(n, MB)), dim3(MB), 0, s, n, lv.diag, bad + 1);
             DSM_HIP(hipGetLastError());
         }
-        DSM_HIP(hipMemcpyAsync(hb, bad, sizeof(hb), hipMemcpyDeviceToHost, s));
+        DSM_HIP(hipMemcpyAsync(hb, bad, hb_bytes, hipMemcpyDeviceToHost, s));
         DSM_HIP(hipStreamSynchronize(s));
         DSM_CHECK(hb[0] == 0, DSM_E_INVALID,
                   "level " + std::to_string(l) + ": " + std::to_string(hb[0]) +
@@ -1109,7 +1111,7 @@ static void build_level(dsm_mg_s *mg, int l, dsm_matrix A, const int32_t *colour
             DSM_HIP(hipMemcpyAsync(lv.offnd, offnd.data(), sizeof(int32_t) * offnd.size(), hipMemcpyHostToDevice, s));
         lv.dperm = (double *)mg->alloc(sizeof(double) * (size_t)std::max<i64>(P.ndiag * P.pitch, 1));
         // parting of the colours' diagonals (k_symgs_list)
-        bool part = n >= PART_ROWS && (P.ndiag == 7 || P.ndiag == 27);
+        bool part = parts;
         for (int c = 0; c < ncol; c++) part = part && !(hb[2 + 2 * c] & hb[3 + 2 * c]);
         if (part) {
             std::vector<int32_t> tab(2 * (size_t)(ncol * P.ndiag), 0);  // offsets by slot, then slots by diagonal
@@ -1154,7 +1156,7 @@ static void build_level(dsm_mg_s *mg, int l, dsm_matrix A, const int32_t *colour
         }
         DSM_HIP(hipStreamSynchronize(s));
     }
-    if (by_colours(lv)) {
+    if (mg->extras && by_colours(lv)) {
         lv.first = (double *)mg->alloc(sizeof(double) * (size_t)n);
         hipLaunchKernelGGL(k_mg_zero, dim3(grid_for(n, MB)), dim3(MB), 0, s, n, lv.first, (const int *)nullptr);
         if (lv.cstart[1] > 0)
@@ -1248,6 +1250,36 @@ using namespace dsm;
 
 static size_t pcg_partials(int64_t n) { return (size_t)dot_partials_cap(n); }
 
+static dsm_mg build_hierarchy(dsm_ctx ctx, int nlevels, const dsm_matrix *levels, const int32_t *const *f2c,
+                              const int32_t *const *colour, bool extras, hipStream_t s) {
+    auto *mg = new dsm_mg_s();
+    mg->ctx = ctx;
+    mg->extras = extras;
+    try {
+        mg->L.resize(nlevels);
+        for (int l = 0; l < nlevels; l++)
+            build_level(mg, l, levels[l], colour[l], l + 1 < nlevels ? f2c[l] : nullptr,
+                        l + 1 < nlevels ? levels[l + 1]->nrows : 0, s);
+        const int64_t n = levels[0]->nrows;
+        const size_t nb = sizeof(double) * (size_t)std::max<int64_t>(n, 1);
+        mg->r = (double *)mg->alloc(nb);
+        mg->z = (double *)mg->alloc(nb);
+        mg->p = (double *)mg->alloc(nb);
+        mg->q = (double *)mg->alloc(nb);
+        mg->xw = (double *)mg->alloc(nb);
+        mg->part_a = (double *)mg->alloc(sizeof(double) * pcg_partials(n));
+        mg->part_b = (double *)mg->alloc(sizeof(double) * pcg_partials(n));
+        mg->part_c = (double *)mg->alloc(sizeof(double) * pcg_partials(n));
+        mg->st = (CgState *)mg->alloc(sizeof(CgState));
+    } catch (...) {
+        (void)hipStreamSynchronize(s);
+        mg->release();
+        delete mg;
+        throw;
+    }
+    return mg;
+}
+
 DSM_API dsm_status dsm_mg_create(dsm_ctx ctx, int32_t nlevels, const dsm_matrix *levels, const int32_t *const *f2c,
                                  const int32_t *const *colour, void *stream, dsm_mg *out) {
     return guard([&] {
@@ -1265,30 +1297,17 @@ DSM_API dsm_status dsm_mg_create(dsm_ctx ctx, int32_t nlevels, const dsm_matrix 
             DSM_CHECK(f2c[l] || levels[l + 1]->nrows == 0, DSM_E_INVALID, "null f2c array");
         DSM_HIP(hipSetDevice(ctx->device));
         hipStream_t s = (hipStream_t)stream;
-        auto *mg = new dsm_mg_s();
-        mg->ctx = ctx;
-        mg->L.resize(nlevels);
-        try {
-            for (int l = 0; l < nlevels; l++)
-                build_level(mg, l, levels[l], colour[l], l + 1 < nlevels ? f2c[l] : nullptr,
-                            l + 1 < nlevels ? levels[l + 1]->nrows : 0, s);
-            const int64_t n = levels[0]->nrows;
-            const size_t nb = sizeof(double) * (size_t)std::max<int64_t>(n, 1);
-            mg->r = (double *)mg->alloc(nb);
-            mg->z = (double *)mg->alloc(nb);
-            mg->p = (double *)mg->alloc(nb);
-            mg->q = (double *)mg->alloc(nb);
-            mg->xw = (double *)mg->alloc(nb);
-            mg->part_a = (double *)mg->alloc(sizeof(double) * pcg_partials(n));
-            mg->part_b = (double *)mg->alloc(sizeof(double) * pcg_partials(n));
-            mg->part_c = (double *)mg->alloc(sizeof(double) * pcg_partials(n));
-            mg->st = (CgState *)mg->alloc(sizeof(CgState));
-        } catch (...) {
-            (void)hipStreamSynchronize(s);
-            mg->release();
-            delete mg;
-            throw;
+        // under a budget, or where the device has no room, without the extras
+        dsm_mg mg = nullptr;
+        if (ctx->budget == 0) {
+            try {
+                mg = build_hierarchy(ctx, nlevels, levels, f2c, colour, true, s);
+            } catch (const Error &e) {
+                if (e.status != DSM_E_NOMEM) throw;
+                clear_error();
+            }
         }
+        if (!mg) mg = build_hierarchy(ctx, nlevels, levels, f2c, colour, false, s);
         *out = mg;
     });
 }

@@ -101,3 +101,56 @@ def test_creation_and_hyb(name):
     assert np.max(np.abs(y - yref) / np.maximum(scale, 1e-300)) <= 1e-14
     A.close()
     c.close()
+
+
+@pytest.mark.parametrize("fmt", ["csr", "dia"])
+def test_hierarchy(fmt):
+    """What a hierarchy holds: per level the rows by colour, the colours' starts and the diagonal (and, DIA,
+    the other offsets, the diagonals by colour and the records of the LDS sweep); r and x of the coarser
+    levels; five vectors, partial sums and the state of the solve.  Level 0 (110,592 rows) would be parted
+    without a budget."""
+    from test_gpu_mg import oracle_levels
+    torch, dev = torch_dev()
+    L = inputs.hpcg27_levels(48, 3)
+    ns = [lv["problem"].nrows for lv in L]
+
+    def hierarchy(budget):
+        c = dsm.Context(0, hbm_budget=budget)
+        mats = []
+        for lv in L:
+            p = lv["problem"]
+            A = dsm.Matrix.from_csr(c, p.nrows, p.ncols, p.row_ptr, p.col, p.val)
+            mats.append(A.convert(fmt) if fmt != "csr" else A)
+        held = c.bytes_in_use()
+        mg = dsm.Multigrid(c, mats, [lv["f2c"] for lv in L[:-1]], [lv["colour"] for lv in L])
+        return c, mats, mg, held
+
+    c, mats, mg, held = hierarchy(0)
+    p = L[0]["problem"]
+    b = torch.from_numpy(p.b).to(dev)
+    _, want = mg.pcg(b, tol=1e-9)
+    mg.close()
+    [A.close() for A in mats]
+    c.close()
+    need = 0
+    for l, (lv, n) in enumerate(zip(L, ns)):
+        nc = int(lv["colour"].max()) + 1
+        need += 4 * n + 8 * (nc + 1) + 8 * n
+        if fmt == "dia":
+            need += 4 * 26 + 8 * 27 * ((n + 63) // 64 * 64)
+            if np.bincount(lv["colour"]).max() <= 512 and n <= 8192:
+                need += 8 * n * 28
+        need += 16 * n if l else 0
+        need += 4 * ns[l + 1] if l + 1 < len(L) else 0
+    need += 5 * 8 * ns[0] + 3 * 8 * max(ns[0] // 256 + 2, 512) + 72
+    # (converting to DIA needs room for both formats, more than the hierarchy does)
+    c, mats, mg, h = hierarchy(held + need if fmt == "csr" else 1 << 30)
+    assert h == held and c.bytes_in_use() == held + need
+    z = mg.apply(b)
+    zr = oracle.mg(oracle_levels(L), p.b)
+    assert np.max(np.abs(z.cpu().numpy() - zr)) <= 1e-12 * np.max(np.abs(zr))
+    _, res = mg.pcg(b, tol=1e-9)
+    assert res["status"] == want["status"] == "converged" and abs(res["iters"] - want["iters"]) <= 1
+    mg.close()
+    [A.close() for A in mats]
+    c.close()
