@@ -21,16 +21,6 @@ uint64_t next_payload_id() {
 
 constexpr size_t POOL_MAX = (size_t)2 << 30;  // bytes a context keeps (under 1% of the device)
 
-// Sizes are rounded up so that blocks of nearly equal size serve each other:
-// by at most 1/16, and only to 256 bytes under a budget, which then bounds the
-// memory held to the byte rounding.
-static size_t pool_class(dsm_ctx ctx, size_t bytes) {
-    size_t step = 256;
-    if (!ctx->budget)
-        while (step * 16 < bytes) step <<= 1;
-    return (bytes + step - 1) / step * step;
-}
-
 // Gives the oldest blocks back until at most `keep` bytes are held.
 static void pool_trim(dsm_ctx ctx, size_t keep) {
     BlockPool::Block b;
@@ -81,7 +71,7 @@ void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s) {
     } else {
         ctx->in_use += bytes;
     }
-    const size_t cls = pool_class(ctx, bytes);
+    const size_t cls = block_class(bytes, ctx->budget != 0);
     void *p = pool_take(ctx, cls, s);
     if (p) return p;
     if (ctx->budget) {  // kept blocks leave room under the budget for the new one
@@ -89,14 +79,26 @@ void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s) {
         const size_t used = ctx->in_use.load();
         pool_trim(ctx, ctx->budget > used ? ctx->budget - used : 0);
     }
-    hipError_t e = hipMalloc(&p, cls);
-    if (e != hipSuccess) {
+    hipError_t e = hipSuccess;
+    bool tight = false;
+    auto obtain = [&](size_t n) -> void * {
+        void *q = nullptr;
+        e = hipMalloc(&q, n);
+        if (e == hipSuccess) return q;
         (void)hipGetLastError();
-        pool_release(ctx);
-        e = hipMalloc(&p, cls);
+        return nullptr;
+    };
+    p = new_block(bytes, cls, obtain, [&] { pool_release(ctx); }, &tight);
+    if (p && tight) {
+        try {
+            std::lock_guard<std::mutex> lk(ctx->pool_mu);
+            ctx->tight.insert(p);
+        } catch (const std::bad_alloc &) {
+            (void)hipFree(p);
+            p = nullptr;
+        }
     }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
+    if (!p) {
         ctx->in_use -= bytes;
         fail(DSM_E_NOMEM, "hipMalloc(" + std::to_string(bytes) + ") failed: " + hipGetErrorString(e));
     }
@@ -106,10 +108,10 @@ void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s) {
 void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s, bool unused) {
     if (!p) return;
     if (bytes == 0) bytes = 16;
-    const size_t cls = pool_class(ctx, bytes);
+    const size_t cls = block_class(bytes, ctx->budget != 0);
     try {
         std::lock_guard<std::mutex> lk(ctx->pool_mu);
-        size_t keep = POOL_MAX;
+        size_t keep = ctx->tight.erase(p) ? 0 : POOL_MAX;
         if (ctx->budget) keep = std::min(keep, ctx->budget - std::min(ctx->budget, ctx->in_use.load() - bytes));
         if (cls <= keep) {
             pool_trim(ctx, keep - cls);

@@ -6,6 +6,7 @@
 #include <atomic>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -29,6 +30,7 @@ struct dsm_ctx_s {
     // (dev_alloc).
     std::mutex pool_mu;
     dsm::BlockPool pool;
+    std::set<void *> tight;  // blocks smaller than their class (new_block)
 };
 
 #include "admission.hpp"

@@ -14,6 +14,31 @@
 
 namespace dsm {
 
+// Sizes are rounded up so that blocks of nearly equal size serve each other:
+// by less than 1/8, and only to 256 bytes under a budget, which then bounds the
+// memory held to the byte rounding.
+inline size_t block_class(size_t bytes, bool budget) {
+    size_t step = 256;
+    if (!budget)
+        while (step * 16 < bytes) step <<= 1;
+    return (bytes + step - 1) / step * step;
+}
+
+// New device memory for `bytes`: a block of their class, if need be after the
+// kept blocks have been given back, or else, where the device has room for the
+// bytes but not for the class, one of the bytes alone (*tight: it must not be
+// kept as one of the class).  obtain(n): a block of n bytes or null.
+template <class Obtain, class GiveBack>
+void *new_block(size_t bytes, size_t cls, Obtain &&obtain, GiveBack &&give_back, bool *tight) {
+    *tight = false;
+    if (void *p = obtain(cls)) return p;
+    give_back();
+    if (void *p = obtain(cls)) return p;
+    if (bytes >= cls) return nullptr;
+    *tight = true;
+    return obtain(bytes);
+}
+
 class BlockPool {
 public:
     using Stream = const void *;

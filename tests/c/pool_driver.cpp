@@ -65,6 +65,27 @@ int main() {
         CHECK(p.take(256, any, &b, &wait) && b.p == mem && !wait);
         CHECK(p.take(256, any, &b, &wait) && wait);
     }
+    // a device with room for the bytes, but not for their class, before or after kept blocks go back
+    for (size_t bytes : {(size_t)1, (size_t)256, (size_t)4097, (size_t)100000, ((size_t)1 << 34) + 1})
+        for (bool budget : {false, true}) {
+            const size_t cls = dsm::block_class(bytes, budget);
+            CHECK(cls >= bytes && cls % 256 == 0 && cls - bytes <= (budget ? 255 : bytes / 8 + 255));
+            CHECK(budget || dsm::block_class(cls, false) == cls);
+            for (size_t room : {bytes - 1, bytes, cls - 1, cls})
+                for (size_t kept : {(size_t)0, cls}) {
+                    if (room < bytes - 1) continue;
+                    size_t left = room - (room < kept ? 0 : kept), tries = 0;
+                    bool tight = false, back = false;
+                    auto obtain = [&](size_t n) -> void * {
+                        tries++;
+                        return n <= left ? mem : nullptr;
+                    };
+                    void *p = dsm::new_block(bytes, cls, obtain, [&] { left = room; back = true; }, &tight);
+                    CHECK((p != nullptr) == (room >= bytes));
+                    CHECK(!p || tight == (room < cls));
+                    CHECK(tries <= 3 && (back || left >= cls));
+                }
+        }
     if (!fails) std::printf("pool driver ok\n");
     return fails != 0;
 }
