@@ -141,6 +141,10 @@ inline unsigned grid_for(i64 n, int per_block) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
+// End of the batch of `step` entries that starts at e, of a run that ends at e1
+// > e: the run may end within a batch of 2^31, where e + step overflows.
+__host__ __device__ __forceinline__ int batch_end(int e, int e1, int step) { return e1 - e > step ? e + step : e1; }
+
 // Workgroups are dealt to the XCDs round-robin (workgroup b runs on XCD
 // b % 8).  Remapping b so that each XCD receives one contiguous range of
 // logical tiles keeps neighbouring tiles - and the vector entries they share

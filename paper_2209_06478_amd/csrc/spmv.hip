@@ -310,17 +310,17 @@ __global__ void __launch_bounds__(SB) k_csr_stream(int nblocks, const i32 *__res
             X xv[CSR_E];
 #pragma unroll
             for (int k = 0; k < CSR_E; k++) xv[k] = x[cc[k]];
-            const int end = min(e + WCE, e1);
-            int row = r + (lane >> lg);
-            i32 a = rp[min(row, r1)], z = rp[min(row + 1, r1)];
-            if (e + WCE < e1) load(e + WCE, cn, vn);
+            const int end = batch_end(e, e1, WCE);
+            u32 row = (u32)r + (lane >> lg);  // (may pass 2^31)
+            i32 a = rp[min(row, (u32)r1)], z = rp[min(row + 1, (u32)r1)];
+            if (end < e1) load(end, cn, vn);
 #pragma unroll
             for (int k = 0; k < CSR_E; k++) prod[lane + k * WAVE] = widen<X>(vv[k]) * xv[k];
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             for (;;) {
-                const bool on = row < r1 && (a < end || z <= end);
+                const bool on = row < (u32)r1 && (a < end || z <= end);
                 const int lo = max(a, e) - e, hi = min(z, end) - e, cut = min(hi, lo + (OWN << lg));
                 X s4[4] = {0, 0, 0, 0};
                 if (on) {
@@ -348,11 +348,11 @@ __global__ void __launch_bounds__(SB) k_csr_stream(int nblocks, const i32 *__res
                     break;
                 }
                 carry = 0;
-                row = r + (lane >> lg);
-                a = rp[min(row, r1)];
-                z = rp[min(row + 1, r1)];
+                row = (u32)r + (lane >> lg);
+                a = rp[min(row, (u32)r1)];
+                z = rp[min(row + 1, (u32)r1)];
             }
-            e += WCE;
+            e = end;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(SB) k_csr_stream(int nblocks, const i32 *__res
             step(c[1], v[1], c[0], v[0]);
         }
         if constexpr (!ACC)
-            for (int row = r + lane; row < r1; row += WAVE) y[row] = 0;  // no entries at all
+            for (u32 row = (u32)r + lane; row < (u32)r1; row += WAVE) y[row] = 0;  // no entries at all
     };
 
     if (w < nb && !(longs >> w & 1)) {

@@ -86,11 +86,11 @@ __device__ __forceinline__ void wg_spmv_csr(const WaveRows &R, int L, const i32 
         }
     };
     auto step = [&](i32 (&cc)[WB], V (&vv)[WB], i32 (&cn)[WB], V (&vn)[WB]) {
-        if (e + WCH < e1) load(e + WCH, cn, vn);
+        const int end = batch_end(e, e1, WCH);
+        if (end < e1) load(end, cn, vn);
 #pragma unroll
         for (int k = 0; k < WB; k++) prod[lane + k * WAVE] = widen<X>(vv[k]) * p[cc[k]];
         wave_fence();
-        const int end = min(e + WCH, e1);
         for (;;) {
             const int row = r + lane / L;
             const int a = row < r1 ? rp[row] : end, z = row < r1 ? rp[row + 1] : end + 1;
@@ -115,7 +115,7 @@ __device__ __forceinline__ void wg_spmv_csr(const WaveRows &R, int L, const i32 
             if (whole < per) break;
         }
         wave_fence();
-        e += WCH;
+        e = end;
     };
     if (e < e1) load(e, c[0], v[0]);
     while (e < e1) {
