@@ -66,6 +66,15 @@ __device__ __forceinline__ void for_each_entry(i64 nrows, const i32 *rp, F f) {
 
 static unsigned entry_grid(i64 nrows) { return grid_for(nrows, EB_ROWS); }
 
+// launch(first, count) for `groups` workgroups of CB threads, some at a time:
+// a launch's threads are counted in 32 bits, and kernels of several threads a
+// row have more for 2^31 rows.
+template <class F>
+static void in_launches(i64 groups, F launch) {
+    constexpr i64 MOST = 1 << 23;
+    for (i64 first = 0; first < groups; first += MOST) launch(first, (unsigned)std::min(MOST, groups - first));
+}
+
 // Privatised counting for histograms whose keys repeat heavily inside a
 // workgroup (the diagonals of a banded matrix, the row lengths of a regular
 // one): one global atomic per entry on a handful of bins serialises at the
@@ -382,8 +391,8 @@ __global__ void k_coo_rowptr(i64 nnz, i64 nrows, i64 ncols, const i32 *row, cons
 // set.  HPCG 104^3: 107 us with a search of the row per entry and a store
 // each, now 40 us.
 constexpr int MARK_L = 8;
-__global__ void __launch_bounds__(CB) k_diag_mark(i64 nrows, const i32 *rp, const i32 *col, i32 *flag) {
-    const i64 r = ((i64)blockIdx.x * CB + threadIdx.x) / MARK_L;
+__global__ void __launch_bounds__(CB) k_diag_mark(i64 first, i64 nrows, const i32 *rp, const i32 *col, i32 *flag) {
+    const i64 r = ((first + blockIdx.x) * CB + threadIdx.x) / MARK_L;
     if (r >= nrows) return;
     const i64 e1 = rp[r + 1];
     i32 *f = flag + (nrows - 1 - r);
@@ -397,6 +406,12 @@ __global__ void __launch_bounds__(CB) k_diag_mark(i64 nrows, const i32 *rp, cons
         for (int u = 0; u < 4; u++)
             if (t[u] == 0) f[c[u]] = 1;
     }
+}
+
+static void diag_mark(i64 nrows, const i32 *rp, const i32 *col, i32 *flag, hipStream_t s) {
+    in_launches((nrows + CB / MARK_L - 1) / (CB / MARK_L), [&](i64 first, unsigned g) {
+        hipLaunchKernelGGL(k_diag_mark, dim3(g), dim3(CB), 0, s, first, nrows, rp, col, flag);
+    });
 }
 
 // Entries per diagonal (index col - row + nrows - 1).  `table`: the span of
@@ -463,12 +478,12 @@ struct RowGroup {
     const W *v;  // entry e of the group: c[e], v[e]
     i64 r0, e0;
 
-    // Loads the row pointers and, where they fit, the entries of rows
+    // Loads the row pointers and, where they fit, the entries of the group's rows
     // [r0, r0 + RG); rows past nrows are empty.  Ends with a barrier.
-    __device__ __forceinline__ RowGroup(i64 nrows, const i32 *rp, const i32 *col, const W *val, int cap, char *lds,
-                                        i32 *srp_)
+    __device__ __forceinline__ RowGroup(i64 group, i64 nrows, const i32 *rp, const i32 *col, const W *val, int cap,
+                                        char *lds, i32 *srp_)
         : srp(srp_) {
-        r0 = (i64)blockIdx.x * RG;
+        r0 = group * RG;
         e0 = rp[min(r0, nrows)];
         for (int t = threadIdx.x; t <= RG; t += CB) srp[t] = (i32)(rp[min(r0 + t, nrows)] - e0);
         __syncthreads();
@@ -495,11 +510,12 @@ struct RowGroup {
 // has no entry.  Bound by its 360 MB read and 243 MB written at HPCG 104^3:
 // 265 us + 32 us of clearing for a scatter of single entries, now 135 us (4.5 TB/s).
 template <class W>
-__global__ void __launch_bounds__(CB) k_dia_fill(i64 nrows, const i32 *rp, const i32 *col, const W *val, i64 ndiag,
-                                                 const i32 *offs, i64 pitch, W *dval, int cap) {
+__global__ void __launch_bounds__(CB) k_dia_fill(i64 group0, i64 nrows, const i32 *rp, const i32 *col,
+                                                 const W *val, i64 ndiag, const i32 *offs, i64 pitch, W *dval,
+                                                 int cap) {
     extern __shared__ __align__(16) char rg_lds[];
     __shared__ i32 srp[RG + 1];
-    const RowGroup<W> G(nrows, rp, col, val, cap, rg_lds, srp);
+    const RowGroup<W> G(group0 + blockIdx.x, nrows, rp, col, val, cap, rg_lds, srp);
     const int row = threadIdx.x % RG, part = __builtin_amdgcn_readfirstlane(threadIdx.x / RG);  // a wave per part
     const i64 i = G.r0 + row;
     const int k0 = (int)(ndiag * part / RGP), k1 = (int)(ndiag * (part + 1) / RGP);
@@ -611,12 +627,12 @@ struct EllSlots {
 // Bound by its 243 MB read and 360 MB written at HPCG 104^3 from DIA: 1031 us
 // with a row per thread, each load behind the last test, now 148 us (4.1 TB/s).
 template <class W, class Slots, bool MERGE>
-__global__ void __launch_bounds__(CB) k_slots_to_csr(i64 nrows, i64 nk, Slots S, const i32 *xrp, const i32 *xcol,
-                                                     const W *xval, const i32 *orp, i32 *ocol, W *oval, int cap) {
+__global__ void __launch_bounds__(CB) k_slots_to_csr(i64 group0, i64 nrows, i64 nk, Slots S, const i32 *xrp,
+                                                     const i32 *xcol, const W *xval, const i32 *orp, i32 *ocol, W *oval, int cap) {
     extern __shared__ __align__(16) char rg_lds[];
     __shared__ i32 srp[RG + 1];
     __shared__ i32 cnt[2][RGP][RG];
-    const i64 r0 = (i64)blockIdx.x * RG;
+    const i64 r0 = (group0 + blockIdx.x) * RG;
     const i64 e0 = orp[r0];
     for (int t = threadIdx.x; t <= RG; t += CB) srp[t] = (i32)(orp[min(r0 + t, nrows)] - e0);
     __syncthreads();
@@ -698,11 +714,11 @@ __global__ void __launch_bounds__(CB) k_slots_to_csr(i64 nrows, i64 nk, Slots S,
 // -1 column sentinel and a zero value after the row's end and in the pitch
 // padding rows (so no memset is needed first).
 template <class W>
-__global__ void __launch_bounds__(CB) k_ell_fill(i64 nrows, i64 pitch, const i32 *rp, const i32 *col, const W *val,
-                                                 i64 K, i32 *ecol, W *eval, int cap) {
+__global__ void __launch_bounds__(CB) k_ell_fill(i64 group0, i64 nrows, i64 pitch, const i32 *rp, const i32 *col,
+                                                 const W *val, i64 K, i32 *ecol, W *eval, int cap) {
     extern __shared__ __align__(16) char rg_lds[];
     __shared__ i32 srp[RG + 1];
-    const RowGroup<W> G(nrows, rp, col, val, cap, rg_lds, srp);
+    const RowGroup<W> G(group0 + blockIdx.x, nrows, rp, col, val, cap, rg_lds, srp);
     const int row = threadIdx.x % RG, part = __builtin_amdgcn_readfirstlane(threadIdx.x / RG);  // a wave per part
     const i64 i = G.r0 + row;
     const int a = srp[row], len = srp[row + 1] - a;
@@ -850,8 +866,7 @@ static void dia_from_csr(dsm_matrix m, const Payload &C, Payload &P, const i32 *
     const i32 *use_flag = flag_true;
     if (!flag_true) {
         DSM_HIP(hipMemsetAsync(flag.p, 0, sizeof(i32) * (size_t)span, s));
-        if (n > 0)
-            hipLaunchKernelGGL(k_diag_mark, dim3(grid_for(n * MARK_L, CB)), dim3(CB), 0, s, n, C.rp, C.col, flag.as<i32>());
+        diag_mark(n, C.rp, C.col, flag.as<i32>(), s);
         DSM_HIP(hipGetLastError());
         use_flag = flag.as<i32>();
     }
@@ -881,8 +896,10 @@ static void dia_from_csr(dsm_matrix m, const Payload &C, Payload &P, const i32 *
     }
     if (n > 0 && nd > 0) {
         const int cap = rg_cap(C.csr_nnz, n);
-        hipLaunchKernelGGL((k_dia_fill<W>), dim3((unsigned)(P.pitch / RG)), dim3(CB), rg_bytes<W>(cap), s, n, C.rp,
-                           C.col, (const W *)C.val, nd, P.offs, P.pitch, (W *)P.dval, cap);
+        in_launches(P.pitch / RG, [&](i64 group0, unsigned g) {
+            hipLaunchKernelGGL((k_dia_fill<W>), dim3(g), dim3(CB), rg_bytes<W>(cap), s, group0, n, C.rp, C.col,
+                               (const W *)C.val, nd, P.offs, P.pitch, (W *)P.dval, cap);
+        });
     }
     DSM_HIP(hipGetLastError());
     sync(s);
@@ -943,8 +960,10 @@ static Payload from_csr_typed(dsm_matrix m, const Payload &C, int fmt, const dsm
             // so any sweep stays valid)
             if (P.pitch > 0 && K > 0) {
                 const int cap = rg_cap(nnz, n);
-                hipLaunchKernelGGL((k_ell_fill<W>), dim3((unsigned)(P.pitch / RG)), dim3(CB), rg_bytes<W>(cap), s, n,
-                                   P.pitch, C.rp, C.col, (const W *)C.val, K, P.ecol, (W *)P.evl, cap);
+                in_launches(P.pitch / RG, [&](i64 group0, unsigned g) {
+                    hipLaunchKernelGGL((k_ell_fill<W>), dim3(g), dim3(CB), rg_bytes<W>(cap), s, group0, n, P.pitch,
+                                       C.rp, C.col, (const W *)C.val, K, P.ecol, (W *)P.evl, cap);
+                });
             }
             DSM_HIP(hipGetLastError());
             if (fmt == DSM_HYB) {
@@ -1071,10 +1090,11 @@ static Payload to_csr_typed(dsm_matrix m, const Payload &S, hipStream_t s) {
             P.val = P.alloc(ctx, sizeof(W) * (size_t)nnz);
             if (n > 0) {
                 const int cap = rg_cap(nnz, n);
-                hipLaunchKernelGGL((k_slots_to_csr<W, DiaSlots<W>, true>), dim3(grid_for(n, RG)), dim3(CB),
-                                   rg_bytes<W>(cap), s, n, S.ndiag,
-                                   DiaSlots<W>{nc, S.offs, (const W *)S.dval, S.pitch}, xrp, S.col,
-                                   (const W *)S.val, P.rp, P.col, (W *)P.val, cap);
+                in_launches(grid_for(n, RG), [&](i64 group0, unsigned g) {
+                    hipLaunchKernelGGL((k_slots_to_csr<W, DiaSlots<W>, true>), dim3(g), dim3(CB), rg_bytes<W>(cap), s,
+                                       group0, n, S.ndiag, DiaSlots<W>{nc, S.offs, (const W *)S.dval, S.pitch}, xrp,
+                                       S.col, (const W *)S.val, P.rp, P.col, (W *)P.val, cap);
+                });
             }
             DSM_HIP(hipGetLastError());
             break;
@@ -1097,10 +1117,11 @@ static Payload to_csr_typed(dsm_matrix m, const Payload &S, hipStream_t s) {
             P.val = P.alloc(ctx, sizeof(W) * (size_t)nnz);
             if (n > 0) {
                 const int cap = rg_cap(nnz, n);
-                hipLaunchKernelGGL((k_slots_to_csr<W, EllSlots<W>, false>), dim3(grid_for(n, RG)), dim3(CB),
-                                   rg_bytes<W>(cap), s, n, S.K,
-                                   EllSlots<W>{S.ecol, (const W *)S.evl, S.pitch}, cr, S.ccol, (const W *)S.cval,
-                                   P.rp, P.col, (W *)P.val, cap);
+                in_launches(grid_for(n, RG), [&](i64 group0, unsigned g) {
+                    hipLaunchKernelGGL((k_slots_to_csr<W, EllSlots<W>, false>), dim3(g), dim3(CB), rg_bytes<W>(cap), s,
+                                       group0, n, S.K, EllSlots<W>{S.ecol, (const W *)S.evl, S.pitch}, cr, S.ccol,
+                                       (const W *)S.cval, P.rp, P.col, (W *)P.val, cap);
+                });
             }
             DSM_HIP(hipGetLastError());
             sync(s);
@@ -1190,7 +1211,7 @@ StructFeatures structure_features(dsm_matrix m, const Payload &C, double theta, 
         F.hdc_ndiag = exclusive_scan_i32(ctx, flag.as<i32>(), slot.as<i32>(), span, s, true);
         // every diagonal with at least one entry: mark then count
         DSM_HIP(hipMemsetAsync(flag.p, 0, sizeof(i32) * (size_t)span, s));
-        hipLaunchKernelGGL(k_diag_mark, dim3(grid_for(n * MARK_L, CB)), dim3(CB), 0, s, n, C.rp, C.col, flag.as<i32>());
+        diag_mark(n, C.rp, C.col, flag.as<i32>(), s);
         F.ndiag = exclusive_scan_i32(ctx, flag.as<i32>(), slot.as<i32>(), span, s, true);
         unsigned long long h[2];
         DSM_HIP(hipMemcpyAsync(h, acc.p, sizeof(h), hipMemcpyDeviceToHost, s));
