@@ -412,7 +412,10 @@ DSM_API dsm_status dsm_convert(dsm_matrix m, dsm_format fmt, const dsm_convert_o
         m->P.release(m->ctx);
         m->P = np;
         if (fmt == DSM_CSR) m->nnz = np.csr_nnz;
-        if (m->P.fmt != DSM_CSR || m->variant >= CSR_VARIANTS) m->variant = 0;
+        if (m->P.fmt != DSM_CSR || m->variant >= CSR_VARIANTS) {
+            m->variant = 0;
+            m->variant_set = false;
+        }
         m->last_stream = s;
     });
 }
@@ -554,6 +557,7 @@ DSM_API dsm_status dsm_set_variant(dsm_matrix m, int32_t variant) {
                    : (f == DSM_COO ? 1 : ((f == DSM_DIA || f == DSM_HDC) ? DIA_VARIANT_COUNT : SWEEP_VARIANT_COUNT));
         DSM_CHECK(variant >= 0 && variant < maxv, DSM_E_INVALID, "no such kernel variant for this format");
         m->variant = variant;
+        m->variant_set = true;
     });
 }
 

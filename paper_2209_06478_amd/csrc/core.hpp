@@ -153,6 +153,7 @@ struct dsm_matrix_s {
     int64_t nrows = 0, ncols = 0, nnz = 0;
     dsm::Payload P;
     int variant = 0;
+    bool variant_set = false;  // by dsm_set_variant or a selection
     int batch_lanes = 0;  // CSR lanes per row in the one-workgroup solver (0 = by mean row length)
     hipStream_t last_stream = nullptr;
     dsm::Workspace ws;   // SpMV scratch (COO tile carries)

@@ -1196,11 +1196,13 @@ static void build_level(dsm_mg_s *mg, int l, dsm_matrix A, const int32_t *colour
 }
 
 // The product p -> A p finds the caches full of the V-cycle's data.  A DIA
-// matrix whose clusters hold two diagonals and more is then swept from LDS
-// (bit 4), whatever the matrix' own variant, which was chosen for products
-// back to back (HPCG 104^3: 65 -> 53 us).
+// matrix whose clusters hold two diagonals and more is then swept from LDS (bit
+// 4), unless its variant has been set or selected.  An iteration on HPCG's
+// levels with variant 0 and 16: 16^3 94.5 and 93.5 us, 32^3 220.3 and 219.2,
+// 64^3 337.0 and 334.2, 80^3 582.8 and 575.8, 96^3 558.9 and 548.7, 104^3 627.7
+// and 615.2, 112^3 704.3 and 689.2, 128^3 (six clusters) 877.0 and 880.6.
 static int product_variant(dsm_matrix A) {
-    return A->P.fmt == DSM_DIA && 2 * A->P.nclu <= A->P.ndiag ? A->variant | 16 : A->variant;
+    return A->P.fmt == DSM_DIA && !A->variant_set && 2 * A->P.nclu <= A->P.ndiag ? A->variant | 16 : A->variant;
 }
 
 static CgState run_pcg_mg(dsm_mg_s *mg, const double *b, double *x, double tol, long long maxit, int every,

@@ -229,6 +229,7 @@ void select_format(dsm_matrix m, uint32_t mask, const dsm_select_opts &o, dsm_se
                 m->batch_lanes = hit.first == DSM_CSR ? hit.second : 0;
             } else {
                 m->variant = hit.second;
+                m->variant_set = true;
             }
             R.chosen = hit.first;
             R.chosen_variant = hit.second;
@@ -302,6 +303,7 @@ void select_format(dsm_matrix m, uint32_t mask, const dsm_select_opts &o, dsm_se
         {
             std::lock_guard<std::mutex> lk(ctx->cache_mu);
             m->variant = ctx->model_variant[best];
+            m->variant_set = true;
         }
         if (m->P.fmt == DSM_COO) m->variant = 0;
         R.chosen = best;
@@ -456,8 +458,10 @@ void select_format(dsm_matrix m, uint32_t mask, const dsm_select_opts &o, dsm_se
     if (o.target == 1) {
         m->batch_lanes = best_f == DSM_CSR ? best_v : 0;
         m->variant = 0;
+        m->variant_set = false;
     } else {
         m->variant = best_v;
+        m->variant_set = true;
     }
     R.chosen = best_f;
     R.chosen_variant = best_v;
