@@ -314,7 +314,8 @@ __global__ void k_lds_records(i64 n, i64 kd, const double *__restrict__ dval, i6
 
 // DSM_MG_LDS=0 turns the LDS sweep off (small levels then take the
 // one-workgroup sweep through the L2), DSM_MG_ND=0 the fixed-length colour
-// sweeps (the runtime-length sweep then runs), to time one against the other.
+// sweeps (the runtime-length sweep then runs, over all diagonals of a parted
+// level in its colours' order), to time one against the other.
 static bool lds_sweep_on();
 static bool nd_sweep_on();
 
@@ -952,7 +953,7 @@ static void symgs(dsm_mg_s *mg, int l, const double *r, double *x, hipStream_t s
     for (int c = from_zero ? 1 : 0; c < nc; c++) order.push_back(c);
     const size_t forward = order.size();
     for (int c = nc - 2; c >= 0; c--) order.push_back(c);
-    const bool lists = lv.fmt == DSM_DIA && (((P.ndiag == 7 || P.ndiag == 27) && nd_sweep_on()) || !lv.nlow.empty());
+    const bool lists = lv.fmt == DSM_DIA && (P.ndiag == 7 || P.ndiag == 27) && nd_sweep_on();
     bool added = false;
     for (size_t k = 0; k < order.size(); k++) {
         const int c = order[k];
@@ -972,7 +973,8 @@ static void symgs(dsm_mg_s *mg, int l, const double *r, double *x, hipStream_t s
                                P.rp, P.col, (const double *)P.val, lv.diag, r, x, stop);
         } else {
             hipLaunchKernelGGL(k_symgs_dia<GSR>, dim3(grid_for(cnt, MB * GSR)), dim3(MB), 0, s, c0, cnt, lv.rows,
-                               lv.n, P.ndiag - 1, lv.offnd, lv.dperm, P.pitch, r, x, stop);
+                               lv.n, P.ndiag - 1, lv.nlow.empty() ? lv.offnd : lv.loff + c * P.ndiag, lv.dperm,
+                               P.pitch, r, x, stop);
         }
     }
     if (!added) prolong(lv, x, to, s, stop);
