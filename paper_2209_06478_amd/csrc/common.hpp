@@ -141,6 +141,17 @@ inline unsigned grid_for(i64 n, int per_block) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
+// launch(first, count) for `groups` workgroups, some at a time: a launch's
+// threads are counted in 32 bits (what is beyond is dropped without an error),
+// and kernels of several threads a row, or of one per slot, have more for large
+// matrices.  Workgroups of at most 512 threads.
+template <class F>
+inline void in_launches(i64 groups, F launch) {
+    constexpr i64 MOST = 1 << 22;
+    for (i64 first = 0; first < groups; first += MOST)
+        launch(first, (unsigned)(groups - first < MOST ? groups - first : MOST));
+}
+
 // End of the batch of `step` entries that starts at e, of a run that ends at e1
 // > e: the run may end within a batch of 2^31, where e + step overflows.
 __host__ __device__ __forceinline__ int batch_end(int e, int e1, int step) { return e1 - e > step ? e + step : e1; }

@@ -66,15 +66,6 @@ __device__ __forceinline__ void for_each_entry(i64 nrows, const i32 *rp, F f) {
 
 static unsigned entry_grid(i64 nrows) { return grid_for(nrows, EB_ROWS); }
 
-// launch(first, count) for `groups` workgroups of CB threads, some at a time:
-// a launch's threads are counted in 32 bits, and kernels of several threads a
-// row have more for 2^31 rows.
-template <class F>
-static void in_launches(i64 groups, F launch) {
-    constexpr i64 MOST = 1 << 23;
-    for (i64 first = 0; first < groups; first += MOST) launch(first, (unsigned)std::min(MOST, groups - first));
-}
-
 // Privatised counting for histograms whose keys repeat heavily inside a
 // workgroup (the diagonals of a banded matrix, the row lengths of a regular
 // one): one global atomic per entry on a handful of bins serialises at the
@@ -294,8 +285,8 @@ __global__ void k_cast(i64 n, const Wi *in, Wo *out) {
 // Flags a value whose cast to DTO (the cast k_cast applies), widened back,
 // differs from it bit for bit (NaN payloads and the sign of zero included).
 template <class Wi, int DTI, int DTO>
-__global__ void k_values_exact(i64 n, const Wi *in, int *bad) {
-    i64 i = (i64)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void k_values_exact(i64 first, i64 n, const Wi *in, int *bad) {
+    i64 i = (first + blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     Wi w = in[i];
     double d;
@@ -1655,13 +1646,14 @@ bool values_exact(dsm_matrix m, int to, hipStream_t s) {
     DSM_HIP(hipMemsetAsync(flag.p, 0, sizeof(int), s));
     auto check = [&](const void *v, i64 n) {
         if (!v || n <= 0) return;
-        dim3 g(grid_for(n, CB)), b(CB);
-        if (P.vdt == DSM_F64 && to == DSM_F32)
-            hipLaunchKernelGGL((k_values_exact<u64, DSM_F64, DSM_F32>), g, b, 0, s, n, (const u64 *)v, flag.as<int>());
-        else if (P.vdt == DSM_F64)
-            hipLaunchKernelGGL((k_values_exact<u64, DSM_F64, DSM_BF16>), g, b, 0, s, n, (const u64 *)v, flag.as<int>());
-        else
-            hipLaunchKernelGGL((k_values_exact<u32, DSM_F32, DSM_BF16>), g, b, 0, s, n, (const u32 *)v, flag.as<int>());
+        in_launches((n + CB - 1) / CB, [&](i64 first, unsigned g) {
+            auto launch = [&](auto kernel, auto *words) {
+                hipLaunchKernelGGL(kernel, dim3(g), dim3(CB), 0, s, first, n, words, flag.as<int>());
+            };
+            if (P.vdt == DSM_F64 && to == DSM_F32) launch(k_values_exact<u64, DSM_F64, DSM_F32>, (const u64 *)v);
+            else if (P.vdt == DSM_F64) launch(k_values_exact<u64, DSM_F64, DSM_BF16>, (const u64 *)v);
+            else launch(k_values_exact<u32, DSM_F32, DSM_BF16>, (const u32 *)v);
+        });
         DSM_HIP(hipGetLastError());
     };
     // every stored value of the active format (padding slots hold +0, exact)

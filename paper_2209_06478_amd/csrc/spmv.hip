@@ -395,15 +395,16 @@ __global__ void __launch_bounds__(SB) k_csr_stream(int nblocks, const i32 *__res
 }
 
 template <class V, class X, int W, bool ACC, bool NT = false, bool DOT = false>
-__global__ void __launch_bounds__(SB) k_csr_vector(i64 nrows, const i32 *__restrict__ rp, const i32 *__restrict__ col,
-                                                   const V *__restrict__ val, const X *__restrict__ x,
-                                                   X *__restrict__ y, const int *__restrict__ stop,
+__global__ void __launch_bounds__(SB) k_csr_vector(i64 first, i64 nrows, const i32 *__restrict__ rp,
+                                                   const i32 *__restrict__ col, const V *__restrict__ val,
+                                                   const X *__restrict__ x, X *__restrict__ y,
+                                                   const int *__restrict__ stop,
                                                    double *__restrict__ part = nullptr, long long *count = nullptr) {
     if (stop && *stop) return;
     // launch order, not the XCD-aware order: with it the HPCG 104^3 launch
     // fetched 382 instead of 456 MB (no x lines fetched into several L2s)
     // but ran 3% slower, this kernel being bound by gather latency
-    const i64 row = ((i64)blockIdx.x * SB + threadIdx.x) / W;
+    const i64 row = ((first + blockIdx.x) * SB + threadIdx.x) / W;
     const int lane = threadIdx.x % W;
     X s = 0;
     if (row < nrows) {
@@ -431,8 +432,8 @@ __global__ void __launch_bounds__(SB) k_csr_vector(i64 nrows, const i32 *__restr
         double d = row < nrows && lane == 0 ? (double)x[row] * (double)s : 0.0;
         d = block_sum<SB>(d, dred);
         if (threadIdx.x == 0) {
-            part[blockIdx.x] = d;
-            if (count && blockIdx.x == 0) *count += 1;
+            part[first + blockIdx.x] = d;
+            if (count && first + blockIdx.x == 0) *count += 1;
         }
     }
 }
@@ -1103,9 +1104,11 @@ static unsigned csr_launch_nt(dsm_matrix m, const Payload &P, const X *x, X *y, 
     }
     const int W = 1 << variant;  // 2 .. 64
     const unsigned g = grid_for(n * W, SB);
-#define VEC(WW)                                                                                                \
-    DSM_LAUNCH((k_csr_vector<V, X, WW, ACC, NT, DOT>), dim3(g), dim3(SB), 0, s, n, P.rp, P.col, val, x, y, stop, \
-               part, count)
+#define VEC(WW)                                                                                                  \
+    in_launches(g, [&](i64 first, unsigned some) {                                                               \
+        DSM_LAUNCH((k_csr_vector<V, X, WW, ACC, NT, DOT>), dim3(some), dim3(SB), 0, s, first, n, P.rp, P.col, val, x, \
+                   y, stop, part, count);                                                                        \
+    })
     switch (W) {
     case 2: VEC(2); break;
     case 4: VEC(4); break;
