@@ -196,29 +196,34 @@ __global__ void k_rowblock_flags(i64 nrows, const i32 *rp, i32 *flag) {
     flag[i] = f;
 }
 
-// pos[nrows], the number of blocks, has been read: it becomes k_heavy_rows'
-// counter.
-__global__ void k_rowblock_scatter(i64 nrows, const i32 *flag, i32 *pos, i32 *blocks, i64 nblocks) {
+__global__ void k_rowblock_scatter(i64 nrows, const i32 *flag, const i32 *pos, i32 *blocks, i64 nblocks) {
     i64 i = (i64)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nrows && flag[i]) blocks[pos[i]] = (i32)i;
-    if (i == 0) {
-        blocks[nblocks] = (i32)nrows;
-        pos[nrows] = 0;
-    }
+    if (i == 0) blocks[nblocks] = (i32)nrows;
 }
 
-// Entries of rows of more than 32 and four times the mean.  A few workgroups,
-// one atomic each: one per wave took 155 us on a Zipf matrix of 1M rows.
-__global__ void __launch_bounds__(CB) k_heavy_rows(i64 nrows, const i32 *rp, i32 *heavy) {
+// What decides how a large matrix' row blocks are swept.  out[0]: entries of
+// rows of more than 32 and four times the mean; out[1], out[2]: of the pairs of
+// neighbouring rows that start at every STEP-th row, those with entries, and
+// those whose first columns lie more than FAR apart.  A few workgroups, one
+// atomic each: one per wave took 155 us on a Zipf matrix of 1M rows.
+constexpr int STRUCT_STEP = 16, STRUCT_FAR = 1024;
+__global__ void __launch_bounds__(CB) k_row_structure(i64 nrows, const i32 *rp, const i32 *col, i32 *out) {
     __shared__ i32 lds[CB / WAVE];
     const i64 long_row = max(32ll, 4 * (i64)rp[nrows] / nrows);
-    i32 h = 0;
+    i32 n[3] = {0, 0, 0};
     for (i64 i = (i64)blockIdx.x * CB + threadIdx.x; i < nrows; i += (i64)gridDim.x * CB) {
-        const i32 len = rp[i + 1] - rp[i];
-        h += len > long_row ? len : 0;
+        const i32 a = rp[i], b = rp[i + 1];
+        n[0] += b - a > long_row ? b - a : 0;
+        if (i % STRUCT_STEP == 0 && i + 1 < nrows && a < b && b < rp[i + 2]) {
+            n[1]++;
+            n[2] += abs(col[b] - col[a]) > STRUCT_FAR;
+        }
     }
-    h = block_sum<CB>(h, lds);
-    if (threadIdx.x == 0 && h) atomicAdd(heavy, h);
+    for (int k = 0; k < 3; k++) {
+        n[k] = block_sum<CB>(n[k], lds);
+        if (threadIdx.x == 0 && n[k]) atomicAdd(&out[k], n[k]);
+    }
 }
 
 void build_row_blocks(dsm_ctx ctx, Payload &P, i64 nrows, hipStream_t s) {
@@ -235,14 +240,18 @@ void build_row_blocks(dsm_ctx ctx, Payload &P, i64 nrows, hipStream_t s) {
     P.nrblocks = nb;
     P.rblocks = (i32 *)P.alloc(ctx, sizeof(i32) * (size_t)(nb + 1));
     const bool big = nb >= 4096;
-    i32 *heavy = pos.as<i32>() + nrows, h = 0;
+    i32 h[3] = {0, 0, 0};
     hipLaunchKernelGGL(k_rowblock_scatter, dim3(grid_for(nrows, CB)), dim3(CB), 0, s, nrows, flag.as<i32>(),
                        pos.as<i32>(), P.rblocks, nb);
-    if (big) hipLaunchKernelGGL(k_heavy_rows, dim3(256), dim3(CB), 0, s, nrows, P.rp, heavy);
+    if (big) {  // (the flags have been read)
+        DSM_HIP(hipMemsetAsync(flag.p, 0, sizeof(h), s));
+        hipLaunchKernelGGL(k_row_structure, dim3(256), dim3(CB), 0, s, nrows, P.rp, P.col, flag.as<i32>());
+    }
     DSM_HIP(hipGetLastError());
-    if (big) DSM_HIP(hipMemcpyAsync(&h, heavy, sizeof(i32), hipMemcpyDeviceToHost, s));
+    if (big) DSM_HIP(hipMemcpyAsync(h, flag.p, sizeof(h), hipMemcpyDeviceToHost, s));
     DSM_HIP(hipStreamSynchronize(s));
-    P.skewed = h > P.csr_nnz / 8;
+    P.skewed = h[0] > P.csr_nnz / 8;
+    P.scattered = h[2] > h[1] / 2;
 }
 
 // ---------------------------------------------------------------- small kernels

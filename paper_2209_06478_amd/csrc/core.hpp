@@ -67,7 +67,9 @@ struct Payload {
     i64 csr_nnz = 0;
     i32 *rblocks = nullptr;  // adaptive row blocks: nrblocks + 1 row indices
     i64 nrblocks = 0;
-    bool skewed = false;  // rows beyond four times the mean hold much of the matrix (4096 row blocks and more)
+    // (4096 row blocks and more)
+    bool skewed = false;     // rows beyond four times the mean hold much of the matrix
+    bool scattered = false;  // neighbouring rows mostly start far from each other
     // COO (HYB overflow)
     i32 *crow = nullptr, *ccol = nullptr;
     void *cval = nullptr;

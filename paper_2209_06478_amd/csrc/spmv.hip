@@ -1068,11 +1068,22 @@ static void coo_launch(dsm_matrix m, i64 nnz, const i32 *row, const i32 *col, co
 // block.  The stream has one dependent chain
 // per 384 entries and needs about 4 waves a SIMD to hide it: 64^3 (7706 blocks)
 // 24.5 -> 21.0 us, but 32^3 (938) 4.7 -> 6.0 and 400k rows of 4 (3123) 7.7 ->
-// 8.2.  Skewed matrices, where a wave's batches cost different amounts, stay
-// with the workgroup as well: Zipf 1M (19755) 184 us against 192.
-constexpr i64 STREAM_BLOCKS = 4096;
+// 8.2.  Blocks that are one row of more than 1024 entries take four batches and
+// need 16384: 10,000 rows of 1500 34.2 (FP32 vectors 29.0) with the workgroup
+// against 33.6 (32.3), 20,000 99.9 (76.3) against 88.2 (73.0).  The workgroup
+// also keeps skewed matrices, where a wave's batches cost different amounts:
+// Zipf 1M (19755) 184 us against 192; and those whose rows gather from all over
+// x, up to 16M entries, where it has more gathers in flight: 1M rows of 8
+// random columns 52.0 against 57.3, 3 25.4 against 28.3, 2M rows of 8 with FP32
+// vectors 95.6 against 104.0; beyond, 1M rows of 27 211.6 against 190.4 and 4M
+// rows of 8 466 against 460.  Rows that start up to 600 columns apart gain from
+// the stream (8 a row 41.0 -> 39.8, 3 a row at 400 19.5 -> 19.2), at 1600 they
+// lose (21.2 -> 22.2).
+constexpr i64 STREAM_BLOCKS = 4096, STREAM_LONG_BLOCKS = 16384, SCATTER_NNZ = 1 << 24;
 static bool csr_streams(const Payload &P) {
-    return P.nrblocks >= STREAM_BLOCKS && !P.skewed;
+    const bool long_rows = P.csr_nnz > RB_T * P.nrblocks;
+    return P.nrblocks >= (long_rows ? STREAM_LONG_BLOCKS : STREAM_BLOCKS) && !P.skewed &&
+           !(P.scattered && P.csr_nnz < SCATTER_NNZ);
 }
 
 static unsigned rblock_groups(const Payload &P) {
