@@ -94,34 +94,44 @@ constexpr i64 WL_ROWS = 19000;       // 8 bytes a row
 constexpr i64 WL_Q_ROWS = 9500;      // q in LDS too: 16 bytes a row
 constexpr i64 WL_CSR_ROWS = 8000;    // 12 bytes a row beside the 64 KB of products
 constexpr i64 WL_CSR_Q_ROWS = 4800;  // q in LDS too: 20 bytes a row
-constexpr size_t PROD_BYTES = sizeof(double) * NW * WCH;
+
+// Threads of a launch: 1024, or as many as the largest of its systems has rows,
+// rounded up to a power of two; the barriers of idle waves, and their place on
+// the CU, cost small systems more than their work.  One call, CSR, DIA and ELL:
+// 2000 systems of 64 rows 519, 341 and 250 us with 1024 threads, 106, 88 and 81
+// with 64; 1000 of 512 rows 767, 468 and 417, now 451, 312 and 334; one of 64
+// rows 59.7, 42.3 and 30.8, now 38.2, 34.2 and 22.5.  A system's bits do not
+// depend on it: the waves that take part in a CSR product go by its rows.
+static __host__ __device__ int csr_waves(i64 n) { return n <= 64 ? 1 : n <= 128 ? 2 : n <= 256 ? 4 : n <= 512 ? 8 : NW; }
+static __host__ __device__ size_t prod_bytes(int threads) { return sizeof(double) * (threads / WAVE) * WCH; }
 
 static __host__ __device__ size_t lds_vec(i64 n) { return (size_t)(n + (n & 1)) * sizeof(double); }
 static __host__ __device__ bool on_cu(int fmt, i64 n) { return n <= (fmt == DSM_CSR ? WL_CSR_ROWS : WL_ROWS); }
 static __host__ __device__ bool lds_q(int fmt, i64 n) { return n <= (fmt == DSM_CSR ? WL_CSR_Q_ROWS : WL_Q_ROWS); }
-static __host__ __device__ size_t lds_bytes(int fmt, i64 n) {
-    size_t b = fmt == DSM_CSR ? PROD_BYTES : 0;
+static __host__ __device__ size_t lds_bytes(int fmt, i64 n, int threads) {
+    size_t b = fmt == DSM_CSR ? prod_bytes(threads) : 0;
     if (!on_cu(fmt, n)) return b;
     b += 2 * sizeof(double) + lds_vec(n) + (lds_q(fmt, n) ? lds_vec(n) : 0);
     return b + (fmt == DSM_CSR ? (size_t)(n + 2) * sizeof(i32) : 0);
 }
 
-// One system, start to end.  ONCU: p on the CU as above.  A solve is a
+// One system, start to end, by T threads (T < BB: of at most T rows).  ONCU: p
+// on the CU as above.  A solve is a
 // sequence of products q = A p: the first with x0 in p's place, the last
 // with the final x (for the true residual).
 // zero_word: the zero word of the other systems.
-template <bool ONCU>
+template <int T, bool ONCU>
 __device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *lds, char *dyn,
                                           const double *zero_word) {
     const BReq &R = *req;
     const int tid = threadIdx.x;
     const int n = (int)R.n;
     double *prod = (double *)dyn;
-    if (R.fmt == DSM_CSR) dyn += PROD_BYTES;
+    if (R.fmt == DSM_CSR) dyn += prod_bytes(T);
     double *ps = (double *)dyn + 2, *qs = ps + (n + (n & 1));
     i32 *rps = (i32 *)(lds_q(R.fmt, n) ? qs + (n + (n & 1)) : qs);
     const bool ql = ONCU && lds_q(R.fmt, n);
-    WgSum total{lds};
+    WgSum<T> total{lds};
     // element access of the two places p and q can live in
     auto getp = [&](int i) { return ONCU ? ps[i] : R.p[i]; };
     auto setp = [&](int i, double t) {
@@ -134,13 +144,13 @@ __device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *ld
     };
     if (ONCU && tid == 0) ps[-1] = 0.0;
     if (ONCU && R.fmt == DSM_CSR)
-        for (int i = tid; i <= n; i += BB) rps[i] = R.rp[i];
+        for (int i = tid; i <= n; i += T) rps[i] = R.rp[i];
     for (int i = tid; i < n; i += BB) setp(i, R.x[i]);
     WaveRows wrows{};
     if (R.fmt == DSM_CSR) {
         if (ONCU) {
             __syncthreads();  // rps
-            wrows = wave_rows(n, rps);
+            wrows = wave_rows(n, rps, csr_waves(n));
         } else {
             wrows = wave_rows(n, R.rp);
         }
@@ -161,16 +171,16 @@ __device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *ld
         const BReq &R = *again;
         const int zero = ONCU ? -1 : (int)(zero_word - R.p);
         if (R.fmt == DSM_CSR) {
-            if (ONCU && ql) csr_spmv(R, wrows, ps, zero, qs, rps, prod);
+            if (T < BB || (ONCU && ql)) csr_spmv(R, wrows, ps, zero, qs, rps, prod);
             else if (ONCU) csr_spmv(R, wrows, ps, zero, R.q, rps, prod);
             else csr_spmv(R, wrows, R.p, zero, R.q, R.rp, prod);
         } else if (R.fmt == DSM_DIA) {
-            if (ONCU && n <= BB) dia_spmv<1, 16>(R, ps, zero, qs);
+            if (T < BB || (ONCU && n <= BB)) dia_spmv<1, 16>(R, ps, zero, qs);
             else if (ONCU && ql) dia_spmv<2, 8>(R, ps, zero, qs);
             else if (ONCU) dia_spmv<2, 8>(R, ps, zero, R.q);
             else dia_spmv<2, 8>(R, R.p, zero, R.q);
         } else {
-            if (ONCU && n <= BB) ell_spmv<1, 16, true>(R, ps, zero, qs);
+            if (T < BB || (ONCU && n <= BB)) ell_spmv<1, 16, true>(R, ps, zero, qs);
             else if (ONCU && ql) ell_spmv<2, 8, true>(R, ps, zero, qs);
             else if (ONCU) ell_spmv<2, 8, true>(R, ps, zero, R.q);
             else ell_spmv<2, 8, false>(R, R.p, zero, R.q);
@@ -251,9 +261,10 @@ __device__ __forceinline__ void solve_one(const BReq *req, BRes *out, double *ld
     }
 }
 
-__global__ void __launch_bounds__(BB) k_cg_batched(const BReq *__restrict__ reqs, BRes *__restrict__ res, int count,
+template <int T>
+__global__ void __launch_bounds__(T, BB / WAVE / 4) k_cg_batched(const BReq *__restrict__ reqs, BRes *__restrict__ res, int count,
                                                    int *next, const double *zero_word) {
-    __shared__ double lds[2 * NW];
+    __shared__ double lds[2 * T / WAVE];
     __shared__ int sidx;
     extern __shared__ char dyn[];  // lds_bytes of the launch's largest system
     for (;;) {
@@ -264,8 +275,8 @@ __global__ void __launch_bounds__(BB) k_cg_batched(const BReq *__restrict__ reqs
         __syncthreads();
         if (idx >= count) return;
         const BReq *req = reqs + idx;
-        if (on_cu(req->fmt, req->n)) solve_one<true>(req, &res[idx], lds, dyn, zero_word);
-        else solve_one<false>(req, &res[idx], lds, dyn, zero_word);
+        if (T < BB || on_cu(req->fmt, req->n)) solve_one<T, true>(req, &res[idx], lds, dyn, zero_word);
+        else solve_one<T, false>(req, &res[idx], lds, dyn, zero_word);
     }
 }
 
@@ -340,11 +351,14 @@ static void launch_reqs(dsm_ctx ctx, std::vector<BReq> &hreq, std::vector<BRes> 
     DSM_HIP(hipMemsetAsync(next, 0, 2 * sizeof(double), s));
     int ncu = 256;
     DSM_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, ctx->device));
-    const unsigned grid = (unsigned)std::min(count, ncu * 4);
+    i64 most = 0;
+    for (auto &R : hreq) most = std::max(most, R.n);
+    const int threads = most <= 64 ? 64 : most <= 128 ? 128 : most <= 256 ? 256 : most <= 512 ? 512 : BB;
+    const unsigned grid = (unsigned)std::min(count, ncu * 4 * (BB / threads));
     size_t dyn = 0;
-    for (auto &R : hreq) dyn = std::max(dyn, lds_bytes(R.fmt, R.n));
-    hipLaunchKernelGGL(k_cg_batched, dim3(grid), dim3(BB), dyn, s, dreq, dres, count, next,
-                       zero_word);
+    for (auto &R : hreq) dyn = std::max(dyn, lds_bytes(R.fmt, R.n, threads));
+    auto kernel = threads == 64 ? k_cg_batched<64> : threads == 128 ? k_cg_batched<128> : threads == 256 ? k_cg_batched<256> : threads == 512 ? k_cg_batched<512> : k_cg_batched<BB>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), dyn, s, dreq, dres, count, next, zero_word);
     DSM_HIP(hipGetLastError());
     DSM_HIP(hipMemcpyAsync(hres.data(), dres, sizeof(BRes) * count, hipMemcpyDeviceToHost, s));
     DSM_HIP(hipStreamSynchronize(s));

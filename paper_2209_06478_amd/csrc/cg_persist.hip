@@ -138,7 +138,7 @@ struct Meeting {
     u64 *slots;
     u32 *outcome;
     int *ok;  // LDS: [0] is 1 until the launch has been given up, [1] the end of kept()
-    WgSum total;
+    WgSum<> total;
     int set = 0;
 
     // v[k]: this thread's part of sum k on entry, the grid's sum on return.
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
         const WaveRows w = wave_rows(rows, rps);
         if (tid % WAVE == 0) wrows[tid / WAVE] = w;
     }
-    Meeting meet{A.slots, A.outcome, ok, WgSum{sums}};
+    Meeting meet{A.slots, A.outcome, ok, WgSum<>{sums}};
 
     // The vector of a product, by column: src as it is, or the direction p =
     // z + beta src (z + nothing where there is no src), z = r or D^-1 r.
@@ -293,7 +293,7 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
     auto publish = [&](X *to, int i, X v) { st_agent(to + r0 + i, v); };
 
     if constexpr (STEP) {
-        WgSum total{sums};
+        WgSum<> total{sums};
         auto put = [&](int k, double v) {
             v = total(v);
             if (tid == 0) A.part[k * PG + blockIdx.x] = v;
@@ -505,7 +505,7 @@ __global__ void __launch_bounds__(BB) k_cg_persist(const CgpArgs A) {
 template <bool JAC>
 __global__ void __launch_bounds__(BB) k_cgp_scalars(const CgpArgs A, int groups, int phase) {
     __shared__ double sums[2 * NW];
-    WgSum total{sums};
+    WgSum<> total{sums};
     auto grid = [&](int k) { return total((int)threadIdx.x < groups ? A.part[k * PG + threadIdx.x] : 0.0); };
     CgState *const st = A.st;
     const bool first = threadIdx.x == 0;

@@ -24,7 +24,7 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// CSR: each wave owns a run of rows with about 1/16 of the entries and
+// CSR: each of `parts` waves owns a run of rows with about as many entries and
 // streams them WCH at a time, coalesced whatever the row lengths; the
 // products go to the wave's LDS buffer, where groups of `lanes` lanes sum
 // the rows, and the next batch's loads are in flight meanwhile.  A row cut by
@@ -35,11 +35,11 @@ struct WaveRows {
     int r, r1, e, e1;  // rows [r, r1) and their entries [e, e1)
 };
 template <class RPP>
-__device__ __forceinline__ WaveRows wave_rows(int n, RPP rp) {
+__device__ __forceinline__ WaveRows wave_rows(int n, RPP rp, int parts = NW) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     // first row whose entries end past the target share
     auto row_at = [&](int t) {
-        const i64 target = rp[0] + (i64)(rp[n] - rp[0]) * t / NW;
+        const i64 target = rp[0] + (i64)(rp[n] - rp[0]) * t / parts;
         int lo = 0, hi = n;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
@@ -49,8 +49,8 @@ __device__ __forceinline__ WaveRows wave_rows(int n, RPP rp) {
         return __builtin_amdgcn_readfirstlane(lo);
     };
     WaveRows R;
-    R.r = w == 0 ? 0 : row_at(w);
-    R.r1 = w == NW - 1 ? n : row_at(w + 1);
+    R.r = w == 0 ? 0 : w < parts ? row_at(w) : n;
+    R.r1 = w >= parts - 1 ? n : row_at(w + 1);
     R.e = __builtin_amdgcn_readfirstlane(rp[R.r]);
     R.e1 = __builtin_amdgcn_readfirstlane(rp[R.r1]);
     return R;
@@ -239,27 +239,33 @@ __device__ __forceinline__ void wg_spmv_ell(int n, int K, int pitch, const i32 *
 }
 
 // Workgroup sum with one barrier: every wave reduces the waves' sums, kept in
-// the half of `lds` (2 * NW doubles) that the sum before did not use.
+// the half of `lds` (2 * T / WAVE doubles) that the sum before did not use.
+// Waves that bring zeros do not change its bits: a sum over fewer threads is
+// the same.
+template <int T = BB>
 struct WgSum {
+    static constexpr int WAVES = T / WAVE;
+    static_assert(WAVES <= 16 && (WAVES & (WAVES - 1)) == 0, "the waves' sums are a part of one DPP row");
     double *lds;
     int half = 0;
     __device__ __forceinline__ double operator()(double v) {
         v = row_sum(v);
-        double *h = lds + (half ^= NW);
+        double *h = lds + (half ^= WAVES);
         if (threadIdx.x % WAVE == 0) h[threadIdx.x / WAVE] = v;
         __syncthreads();
-        return row16_sum(h[threadIdx.x % NW]);
+        return lanes_sum<WAVES>(h[threadIdx.x % WAVES]);
     }
-    // sum over the 16 lanes of a DPP row, in every lane
-    static __device__ __forceinline__ double row16_sum(double v) {
-        v += dpp<0xB1>(v);   // lane ^ 1
-        v += dpp<0x4E>(v);   // lane ^ 2
-        v += dpp<0x141>(v);  // the other quad of the half row
-        v += dpp<0x140>(v);  // the other half row
+    // sum over groups of N lanes of a DPP row, in every lane
+    template <int N>
+    static __device__ __forceinline__ double lanes_sum(double v) {
+        if constexpr (N > 1) v += dpp<0xB1>(v);       // lane ^ 1
+        if constexpr (N > 2) v += dpp<0x4E>(v);       // lane ^ 2
+        if constexpr (N > 4) v += dpp<0x141>(v);      // the other quad of the half row
+        if constexpr (N > 8) v += dpp<0x140>(v);      // the other half row
         return v;
     }
     static __device__ __forceinline__ double row_sum(double v) {
-        v = row16_sum(v);
+        v = lanes_sum<16>(v);
         return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
     }
     template <int CTRL>
@@ -276,6 +282,4 @@ struct WgSum {
         return __builtin_bit_cast(double, (u64)hi << 32 | lo);
     }
 };
-static_assert(NW == 16, "WgSum reduces one DPP row of wave sums");
-
 }  // namespace dsm
