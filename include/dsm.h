@@ -90,8 +90,11 @@ int32_t dsm_version(void);
  * no cap beyond what hipMalloc can give.  Exceeding it fails with
  * DSM_E_NOMEM before anything is allocated.  The context keeps up to 2 GiB of
  * device memory that its calls have freed, for later calls (within the budget
- * when there is one); it is given back when an allocation needs the room and
- * when the context is destroyed. */
+ * when there is one); it is given back when an allocation of the context needs
+ * the room and when the context is destroyed.  With a budget, memory that only
+ * makes calls faster is not taken: HYB keeps no row groups of its overflow (its
+ * products take launches of their own for it), and hierarchies neither part
+ * their levels' diagonals nor keep the first colour's diagonal (dsm_mg_create). */
 dsm_status dsm_ctx_create(int device, size_t hbm_budget_bytes, dsm_ctx *out);
 /* Frees the context.  All its matrices must have been destroyed. */
 dsm_status dsm_ctx_destroy(dsm_ctx ctx);
@@ -428,11 +431,17 @@ typedef struct {
  * iterate on return.  The result is filled for OK, NOT_CONVERGED and
  * BREAKDOWN.  Blocking.  Systems whose rows, and the columns they reach, fit in
  * the LDS of one workgroup per CU (CSR, DIA and ELL, and HDC and HYB that are
- * one of them: an HPCG grid up to about 72^3, a band of 80 up to about 1M
- * rows) run the whole loop in one launch whose workgroups stay on the device
- * (solves in flight at the same time share its CUs out and wait for their
- * turn); DSM_CG_RESIDENT=0 (an environment switch, as are the next two) sends
- * them through the loop of one launch per step that the others take, with
+ * one of them) run the whole loop in one launch whose workgroups stay on the
+ * device.  With FP64 vectors these are HPCG grids up to 78^3 in DIA and ELL and
+ * 61^3 in CSR, which also needs room for products, or matrices that reach 80
+ * columns to each side up to 1.2M and 0.64M rows; refinement's FP32 solves up
+ * to 104^3 and 91^3, 2.5M and 1.6M rows.  Solves in flight at the same time
+ * share the CUs out and wait for their turn; a launch that could not be held on
+ * the device at once is given up after 0.1 s, and its solve, with the next 64
+ * of the handle, goes on step by step, with the same bits (DSM_CG_GIVE_UP=k, an
+ * environment switch, as are the next three, gives the k-th launch of a solve
+ * up, counted from 0).  DSM_CG_RESIDENT=0 sends
+ * all systems through the loop of one launch per step that larger ones take, with
  * results equal up to the order of the sums.  Two switches pick between equivalent executions of that loop:
  * DSM_CG_GRAPH=0 launches it eagerly instead of replaying captured graphs
  * (bitwise the same result), and DSM_CG_FUSED=1 runs the two-kernel iteration
@@ -449,7 +458,7 @@ dsm_status dsm_cg_solve(dsm_matrix m, const double *b, double *x, const dsm_cg_o
  * (x holds x0) and tolerance/maxit from opts[k] (mode must be F64).
  * Systems small enough run whole inside one persistent workgroup each;
  * larger ones are solved one after another on `stream`.  Each system's
- * result is bitwise the same as when it is solved alone.  Blocking. */
+ * result is bitwise the same as in a call of its own.  Blocking. */
 dsm_status dsm_cg_solve_batched(int32_t count, const dsm_matrix *mats, const double *const *b,
                                 double *const *x, const dsm_cg_opts *opts,
                                 dsm_cg_result *results, void *stream);
@@ -558,8 +567,14 @@ typedef struct dsm_mg_s *dsm_mg;
  * DIA levels keep a colour-ordered copy of their diagonals (the level's
  * value bytes again); 7- and 27-diagonal levels whose colours have at most
  * 512 rows also keep a record of (diagonals + 1) x 8 bytes per row and sweep in
- * one workgroup with x in LDS.  Two environment switches pick equivalent
- * executions (same results), for timing one against the other:
+ * one workgroup with x in LDS.  Without a budget, and where the device has
+ * room, levels swept by a launch per colour (more than 8192 rows) also keep the
+ * first colour's diagonal (8 bytes a row), and 7- and 27-diagonal DIA levels of
+ * 65,536 rows and more whose colouring allows it (every diagonal of a colour
+ * leads to lower colours only or to higher ones only) are parted: they keep 8
+ * bytes a row for a V-cycle's sums and a table of offsets per colour, and sum a
+ * row's lower neighbours before its higher ones.  Two environment switches pick
+ * equivalent executions (same results), for timing one against the other:
  * DSM_MG_LDS=0 (small levels sweep through the L2 instead of LDS) and
  * DSM_MG_ND=0 (the runtime-length colour sweep for 7/27 diagonals). */
 dsm_status dsm_mg_create(dsm_ctx ctx, int32_t nlevels, const dsm_matrix *levels, const int32_t *const *f2c,
@@ -570,7 +585,8 @@ dsm_status dsm_mg_destroy(dsm_mg mg);
 
 /* One symmetric Gauss-Seidel sweep on level `level`: x <- S(x) for
  * A_level x = r (forward then backward; r, x device FP64 vectors of the
- * level's size, not aliased).  Asynchronous on `stream`. */
+ * level's size, not aliased).  Asynchronous on `stream`; sweeps with vectors of
+ * their own may overlap, also with dsm_mg_apply. */
 dsm_status dsm_mg_symgs(dsm_mg mg, int32_t level, const double *r, double *x, void *stream);
 
 /* z = M r: one V-cycle from z = 0 (r, z device FP64 vectors of
@@ -580,7 +596,9 @@ dsm_status dsm_mg_apply(dsm_mg mg, const double *r, double *z, void *stream);
 
 /* CG on levels[0] x = b preconditioned by one V-cycle per iteration (HPCG's
  * solver): b, x device FP64 vectors, x holds x0.  opts: tol, maxit,
- * check_every as for dsm_cg_solve (mode is ignored).  The result and
+ * check_every as for dsm_cg_solve (mode is ignored).  A DIA levels[0] whose
+ * variant was neither set nor selected is multiplied with from LDS (variant bit
+ * 4) where its diagonals lie close together.  The result and
  * return value follow dsm_cg_solve; result->relres is the recursive
  * ||r||/||r0||, relres_true = ||b - A x|| / ||b||.  Blocking. */
 dsm_status dsm_pcg_mg_solve(dsm_mg mg, const double *b, double *x, const dsm_cg_opts *opts,

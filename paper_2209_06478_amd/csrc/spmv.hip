@@ -616,8 +616,10 @@ static_assert(DIA_CLUSTER_K <= CLU_MAXK, "a cluster record holds CLU_MAXK relati
 // gathering them from L2: the 27 diagonals of a 27-point stencil need 3
 // window loads instead of 27 gathers.  Columns outside the matrix read +0
 // (their slots are padding, +0); zero slots drop their operand as in k_dia.
-// Measured faster than k_dia beyond the Infinity Cache (HPCG 128^3 and
-// 144^3), slower at 104^3, where k_dia's gathers hit the caches.
+// Faster than k_dia where the caches do not hold matrix and x: cold sweeps of
+// HPCG 104^3 (45.0-45.4 us, with nontemporal values), the product inside
+// multigrid PCG (104^3: 65 -> 53 us) and 128^3 and 144^3 back to back.  Slower
+// back to back at 104^3, where k_dia's gathers hit the caches.
 template <class V, class X, bool ACC, bool XCD, int R, bool P2, bool DOT = false, bool NT = false>
 __global__ void __launch_bounds__(SB) k_dia_lds(i64 nrows, i64 ncols, i64 nclu, const i32 *__restrict__ clu,
                                                 const i32 *__restrict__ offs, const V *__restrict__ dval, i64 pitch,
