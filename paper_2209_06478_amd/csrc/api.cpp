@@ -21,16 +21,20 @@ uint64_t next_payload_id() {
 
 constexpr size_t POOL_MAX = (size_t)2 << 30;  // bytes a context keeps (under 1% of the device)
 
-// Gives the oldest blocks back until at most `keep` bytes are held.
+// Gives the oldest blocks back until at most `keep` bytes are held (hipFree
+// waits for the device: without the lock).
 static void pool_trim(dsm_ctx ctx, size_t keep) {
-    BlockPool::Block b;
-    while (ctx->pool.bytes() > keep && ctx->pool.take_oldest(&b)) (void)hipFree(b.p);
+    for (;;) {
+        BlockPool::Block b;
+        {
+            std::lock_guard<std::mutex> lk(ctx->pool_mu);
+            if (ctx->pool.bytes() <= keep || !ctx->pool.take_oldest(&b)) return;
+        }
+        (void)hipFree(b.p);
+    }
 }
 
-void pool_release(dsm_ctx ctx) {
-    std::lock_guard<std::mutex> lk(ctx->pool_mu);
-    pool_trim(ctx, 0);
-}
+void pool_release(dsm_ctx ctx) { pool_trim(ctx, 0); }
 
 // A kept block of this class that is free of earlier work, or null.  The
 // device is waited for without the lock: other threads go on meanwhile.
@@ -75,7 +79,6 @@ void *dev_alloc(dsm_ctx ctx, size_t bytes, hipStream_t s) {
     void *p = pool_take(ctx, cls, s);
     if (p) return p;
     if (ctx->budget) {  // kept blocks leave room under the budget for the new one
-        std::lock_guard<std::mutex> lk(ctx->pool_mu);
         const size_t used = ctx->in_use.load();
         pool_trim(ctx, ctx->budget > used ? ctx->budget - used : 0);
     }
@@ -109,12 +112,11 @@ void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s, bool unused) {
     if (!p) return;
     if (bytes == 0) bytes = 16;
     const size_t cls = block_class(bytes, ctx->budget != 0);
+    size_t keep = POOL_MAX;
+    if (ctx->budget) keep = std::min(keep, ctx->budget - std::min(ctx->budget, ctx->in_use.load() - bytes));
     try {
         std::lock_guard<std::mutex> lk(ctx->pool_mu);
-        size_t keep = ctx->tight.erase(p) ? 0 : POOL_MAX;
-        if (ctx->budget) keep = std::min(keep, ctx->budget - std::min(ctx->budget, ctx->in_use.load() - bytes));
-        if (cls <= keep) {
-            pool_trim(ctx, keep - cls);
+        if (!ctx->tight.erase(p) && cls <= keep) {
             // while an error is on its way up the call's work may still be
             // queued when it returns, and its stream may be destroyed
             ctx->pool.put(p, cls, std::uncaught_exceptions() ? any_stream() : s, unused);
@@ -123,6 +125,7 @@ void dev_free(dsm_ctx ctx, void *p, size_t bytes, hipStream_t s, bool unused) {
     } catch (const std::bad_alloc &) {
     }
     if (p) (void)hipFree(p);
+    else pool_trim(ctx, keep);  // (the newest block stays)
     ctx->in_use -= bytes;
 }
 
