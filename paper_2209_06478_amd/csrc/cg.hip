@@ -861,7 +861,7 @@ void cg_solve_ws(dsm_matrix m, const double *b, double *x, const dsm_cg_opts &o,
     if (o.mode == DSM_CG_JACOBI) {
         jacobi_dinv(m, B, s);
         CgState h;
-        const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, B.dinv, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every};
+        const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, B.dinv, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every, true};
         if (use_graph && cg_persist<double>(m, S, s, cgws, &h, &R.relres_true)) {
             finish(h);
             return;
@@ -883,7 +883,7 @@ void cg_solve_ws(dsm_matrix m, const double *b, double *x, const dsm_cg_opts &o,
         // passes (with the caller's x in it, a new x meant a new capture).
         CgState h;
         if (use_graph && !fused_ok(m)) {
-            const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, nullptr, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every};
+            const CgpSolve<double> S{b, x, x, B.xw, {B.p, B.p2}, B.r, B.q, 0, nullptr, B.part_a, B.st, o.tol, 0.0, maxit, false, o.check_every, false};
             if (cg_persist<double>(m, S, s, cgws, &h, &R.relres_true)) {
                 finish(h);
                 return;
@@ -969,7 +969,7 @@ void cg_solve_ws(dsm_matrix m, const double *b, double *x, const dsm_cg_opts &o,
         const long long left = std::max<long long>(1, maxit - inner_total);
         CgState h;
         const CgpSolve<float> S{B.r32, nullptr, B.d32, B.q32, {B.p32, B.p32b}, B.ri32, (float *)B.q, last_p, nullptr,
-                                B.part_a, B.st2, tau, pc, left, true, o.check_every};
+                                B.part_a, B.st2, tau, pc, left, true, o.check_every, true};
         if (use_graph && !fused_ok(m) && cg_persist<float>(m, S, s, cgws, &h, nullptr)) {
             last_p = (int)((h.iters + last_p) & 1);
         } else {

@@ -127,6 +127,7 @@ struct CgpSolve {
     long long maxit;
     bool x0_zero;  // x_in is zero (and not read)
     int every;     // iterations per launch; <= 0: chosen by size
+    bool waited;   // the stream has been waited for: it has only the solve's own work
 };
 // Solves and waits; false, with nothing done, when the system does not fit that
 // loop.  The solves in flight on a device share its CUs (a solve waits for its

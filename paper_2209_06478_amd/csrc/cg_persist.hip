@@ -767,7 +767,7 @@ bool cg_persist(dsm_matrix m, const CgpSolve<X> &S, hipStream_t s, Workspace &cg
     bool by_steps = cgws.alone_wait > 0;  // a solve before this one did not get the device
     if (by_steps) cgws.alone_wait--;
     // (what the stream still has to do is done before CUs are asked for)
-    else DSM_HIP(hipStreamSynchronize(s));
+    else if (!S.waited) DSM_HIP(hipStreamSynchronize(s));
     for (int launch = 0; !by_steps; launch++) {
         struct Cus {
             CuShare &share;

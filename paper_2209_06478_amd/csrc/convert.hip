@@ -202,27 +202,30 @@ __global__ void k_rowblock_scatter(i64 nrows, const i32 *flag, const i32 *pos, i
     if (i == 0) blocks[nblocks] = (i32)nrows;
 }
 
-// What decides how a large matrix' row blocks are swept.  out[0]: entries of
-// rows of more than 32 and four times the mean; out[1], out[2]: of the pairs of
-// neighbouring rows that start at every STEP-th row, those with entries, and
-// those whose first columns lie more than FAR apart.  A few workgroups, one
-// atomic each: one per wave took 155 us on a Zipf matrix of 1M rows.
-constexpr int STRUCT_STEP = 16, STRUCT_FAR = 1024;
+// What decides how a large matrix' row blocks are swept, in parts per
+// workgroup.  out[0]: entries of rows of more than 32 and four times the mean;
+// out[1], out[2]: of a pair of neighbouring rows per thread, spread over the
+// matrix, those with entries, and those whose first columns lie more than
+// STRUCT_FAR apart.  A few workgroups, and no atomics (one per wave took 155 us
+// on a Zipf matrix of 1M rows).
+constexpr int STRUCT_GROUPS = 256, STRUCT_FAR = 1024;
 __global__ void __launch_bounds__(CB) k_row_structure(i64 nrows, const i32 *rp, const i32 *col, i32 *out) {
     __shared__ i32 lds[CB / WAVE];
+    const i64 t = (i64)blockIdx.x * CB + threadIdx.x, threads = (i64)STRUCT_GROUPS * CB;
+    const i64 i = t * (nrows - 1) / threads;  // (nrows >= 4096: below nrows - 1)
+    const i32 a = rp[i], b = rp[i + 1];
+    const bool pair = a < b && b < rp[i + 2];
+    const i32 apart = pair ? abs(col[b] - col[a]) : 0;
     const i64 long_row = max(32ll, 4 * (i64)rp[nrows] / nrows);
-    i32 n[3] = {0, 0, 0};
-    for (i64 i = (i64)blockIdx.x * CB + threadIdx.x; i < nrows; i += (i64)gridDim.x * CB) {
-        const i32 a = rp[i], b = rp[i + 1];
-        n[0] += b - a > long_row ? b - a : 0;
-        if (i % STRUCT_STEP == 0 && i + 1 < nrows && a < b && b < rp[i + 2]) {
-            n[1]++;
-            n[2] += abs(col[b] - col[a]) > STRUCT_FAR;
-        }
+    i32 heavy = 0;
+    for (i64 r = t; r < nrows; r += threads) {
+        const i32 len = rp[r + 1] - rp[r];
+        heavy += len > long_row ? len : 0;
     }
+    const i32 n[3] = {heavy, pair, apart > STRUCT_FAR};
     for (int k = 0; k < 3; k++) {
-        n[k] = block_sum<CB>(n[k], lds);
-        if (threadIdx.x == 0 && n[k]) atomicAdd(&out[k], n[k]);
+        const i32 sum = block_sum<CB>(n[k], lds);
+        if (threadIdx.x == 0) out[k * STRUCT_GROUPS + blockIdx.x] = sum;
     }
 }
 
@@ -240,18 +243,18 @@ void build_row_blocks(dsm_ctx ctx, Payload &P, i64 nrows, hipStream_t s) {
     P.nrblocks = nb;
     P.rblocks = (i32 *)P.alloc(ctx, sizeof(i32) * (size_t)(nb + 1));
     const bool big = nb >= 4096;
-    i32 h[3] = {0, 0, 0};
+    i32 h[3 * STRUCT_GROUPS] = {};
     hipLaunchKernelGGL(k_rowblock_scatter, dim3(grid_for(nrows, CB)), dim3(CB), 0, s, nrows, flag.as<i32>(),
                        pos.as<i32>(), P.rblocks, nb);
-    if (big) {  // (the flags have been read)
-        DSM_HIP(hipMemsetAsync(flag.p, 0, sizeof(h), s));
-        hipLaunchKernelGGL(k_row_structure, dim3(256), dim3(CB), 0, s, nrows, P.rp, P.col, flag.as<i32>());
-    }
+    if (big)  // (the flags have been read; 4096 blocks are 4096 rows and more)
+        hipLaunchKernelGGL(k_row_structure, dim3(STRUCT_GROUPS), dim3(CB), 0, s, nrows, P.rp, P.col, flag.as<i32>());
     DSM_HIP(hipGetLastError());
     if (big) DSM_HIP(hipMemcpyAsync(h, flag.p, sizeof(h), hipMemcpyDeviceToHost, s));
     DSM_HIP(hipStreamSynchronize(s));
-    P.skewed = h[0] > P.csr_nnz / 8;
-    P.scattered = h[2] > h[1] / 2;
+    i64 sum[3] = {0, 0, 0};
+    for (int k = 0; k < 3 * STRUCT_GROUPS; k++) sum[k / STRUCT_GROUPS] += h[k];
+    P.skewed = sum[0] > P.csr_nnz / 8;
+    P.scattered = sum[2] > sum[1] / 2;
 }
 
 // ---------------------------------------------------------------- small kernels

@@ -23,7 +23,8 @@ def test_product_kernel(monkeypatch):
             _, res = mg.pcg(b, tol=1e-8)
             torch.cuda.synchronize()
         assert res["status"] == "converged"
-        names = [e.key for e in prof.key_averages() if e.count >= res["iters"]]
+        # (the true residual at the end is one product with the variant as it is)
+        names = [e.key for e in prof.key_averages() if e.count > 2]
         assert any("k_pmg_update_p" in k for k in names), names
         return any("k_dia_lds<" in k for k in names), any("k_dia<" in k for k in names)
 
