@@ -204,18 +204,22 @@ __global__ void k_rowblock_scatter(i64 nrows, const i32 *flag, const i32 *pos, i
 
 // What decides how a large matrix' row blocks are swept, in parts per
 // workgroup.  out[0]: entries of rows of more than 32 and four times the mean;
-// out[1], out[2]: of a pair of neighbouring rows per thread, spread over the
-// matrix, those with entries, and those whose first columns lie more than
-// STRUCT_FAR apart.  A few workgroups, and no atomics (one per wave took 155 us
-// on a Zipf matrix of 1M rows).
-constexpr int STRUCT_GROUPS = 256, STRUCT_FAR = 1024;
+// out[1], out[2]: of 4096 pairs of neighbouring rows, spread over the matrix,
+// those with entries, and those whose first columns lie more than STRUCT_FAR
+// apart.  A few workgroups, and no atomics (one per wave took 155 us on a Zipf
+// matrix of 1M rows).
+constexpr int STRUCT_GROUPS = 512, STRUCT_PAIRS = 4096 / STRUCT_GROUPS, STRUCT_FAR = 1024;
 __global__ void __launch_bounds__(CB) k_row_structure(i64 nrows, const i32 *rp, const i32 *col, i32 *out) {
     __shared__ i32 lds[CB / WAVE];
     const i64 t = (i64)blockIdx.x * CB + threadIdx.x, threads = (i64)STRUCT_GROUPS * CB;
-    const i64 i = t * (nrows - 1) / threads;  // (nrows >= 4096: below nrows - 1)
-    const i32 a = rp[i], b = rp[i + 1];
-    const bool pair = a < b && b < rp[i + 2];
-    const i32 apart = pair ? abs(col[b] - col[a]) : 0;
+    bool pair = false;
+    i32 apart = 0;
+    if (threadIdx.x < STRUCT_PAIRS) {
+        const i64 i = ((i64)blockIdx.x * STRUCT_PAIRS + threadIdx.x) * (nrows - 1) / 4096;  // below nrows - 1
+        const i32 a = rp[i], b = rp[i + 1];
+        pair = a < b && b < rp[i + 2];
+        apart = pair ? abs(col[b] - col[a]) : 0;
+    }
     const i64 long_row = max(32ll, 4 * (i64)rp[nrows] / nrows);
     i32 heavy = 0;
     for (i64 r = t; r < nrows; r += threads) {
