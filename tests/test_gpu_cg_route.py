@@ -4,6 +4,7 @@ launch per step for systems too large or switched off."""
 import pytest
 
 from gpu_common import make_matrix, torch_dev
+from kernel_trace import kernels
 from test_gpu_cg_resident import _problem
 
 pytestmark = pytest.mark.gpu
@@ -11,16 +12,12 @@ pytestmark = pytest.mark.gpu
 
 def test_routes(monkeypatch):
     torch, dev = torch_dev()
-    from torch.profiler import ProfilerActivity, profile
 
     def route(A, b, **kw):
-        """Which of the kernels ran (a trace may lack some of the launches: several solves)."""
-        with profile(activities=[ProfilerActivity.CUDA]) as prof:
-            for _ in range(4):
-                _, res = A.cg(b, tol=1e-9, **kw)
-                assert res["status"] == "converged"
-            torch.cuda.synchronize()
-        names = " ".join(e.key for e in prof.key_averages())
+        """Which of the kernels ran."""
+        def solve():
+            assert A.cg(b, tol=1e-9, **kw)[1]["status"] == "converged"
+        names = kernels(solve)
         return tuple(k in names for k in ("k_slots_clear", "k_cg_persist", "k_cgp_scalars", "k_cg_update_r"))
 
     monkeypatch.setenv("DSM_CG_GRAPH", "0")

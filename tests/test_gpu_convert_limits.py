@@ -8,6 +8,12 @@ from gpu_common import ctx, log, torch_dev
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def _give_memory_back():
+    yield
+    torch_dev()[0].cuda.empty_cache()
+
+
 @pytest.mark.parametrize("fmt", ["dia", "ell", "hdc"])
 def test_more_than_2_30_rows(fmt):
     torch, dev = torch_dev()

@@ -6,6 +6,14 @@ import paper_2209_06478_amd as dsm
 from gpu_common import ctx, log, torch_dev
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _give_memory_back():
+    yield
+    torch_dev()[0].cuda.empty_cache()
+
+
 TOP = 2 ** 31 - 2  # the largest count a matrix may have
 
 

@@ -9,6 +9,7 @@ import pytest
 import oracle
 import paper_2209_06478_amd as dsm
 from gpu_common import ctx, log, row_scaled_err, torch_dev
+from kernel_trace import kernels
 from test_gpu_csr_rows import EDGES
 
 pytestmark = pytest.mark.gpu
@@ -46,7 +47,6 @@ CASES = {
 @pytest.mark.parametrize("name", list(CASES))
 def test_route(name):
     torch, dev = torch_dev()
-    from torch.profiler import ProfilerActivity, profile
     make, streams = CASES[name]
     nr, nc, rp, col = make()
     val = np.random.default_rng(3).standard_normal(col.size)
@@ -54,15 +54,11 @@ def test_route(name):
     yref, scale = oracle.spmv_csr_ref(rp, col, val, x)
     A = dsm.Matrix.from_csr(ctx(), nr, nc, rp, col, val)
     xt = torch.from_numpy(x).to(dev)
-    A.spmv(xt)
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        for _ in range(4):  # (a trace may lack some of the launches)
-            y = A.spmv(xt)
-        torch.cuda.synchronize()
-    names = [e.key for e in prof.key_averages()]
-    log(f"[split] {name}: {[k[:40] for k in names]}")
-    assert any("k_csr_stream" in k for k in names) == streams
-    assert any("k_csr_adaptive" in k for k in names) != streams
+    y = A.spmv(xt)
+    names = kernels(lambda: A.spmv(xt, out=y))
+    log(f"[split] {name}: {names[:80]}")
+    assert ("k_csr_stream" in names) == streams
+    assert ("k_csr_adaptive" in names) != streams
     assert row_scaled_err(y.cpu().numpy(), yref, scale) <= 1e-14
     A.close()
 

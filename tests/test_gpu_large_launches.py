@@ -8,6 +8,12 @@ from gpu_common import ctx, log, torch_dev
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def _give_memory_back():
+    yield
+    torch_dev()[0].cuda.empty_cache()
+
+
 def _sparse(n, rows, per, val, torch, dev):
     counts = torch.zeros(n + 1, dtype=torch.int32, device=dev)
     counts[rows + 1] = per
